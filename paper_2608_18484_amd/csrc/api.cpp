@@ -116,7 +116,7 @@ void describe(const Geom& g, Work* w, Layout& L) {
   add(&w->vperm, g.bf16 ? N * dv * 2 : 0);
   addq(&w->osp, N * dv * 4);
   addq(&w->odp, M * dv * 4);
-  addq(&w->part, M * g.nsplit * (dv + 2) * 4);
+  addq(&w->part, g.part_km ? 0 : M * g.nsplit * (dv + 2) * 4);
   addq(&w->mlst, N * 4 * 4);
   addq(&w->fitv, 3 * dv * 4);
   addq(&w->fity, dv * r * 4);
@@ -143,6 +143,10 @@ void bind(const Geom& g, Work* w, const Layout& L, char* base, int bh, int j = 0
     std::memcpy((char*)w + it.field, &ptr, sizeof ptr);  // every Work member is a pointer
     off += align256((size_t)g.BH * it.per_head * (it.per_query ? g.G : 1));
   }
+  // the probe partials of attend, flat over [G][BH], in the k-means operands
+  // km_xhi and km_xlo (adjacent; only sparsepr_plan uses them)
+  if (g.part_km)
+    w->part = (float*)w->km_xhi + (size_t)j * g.BH * std::max(g.M, 1) * g.nsplit * (g.dv + 2);
 }
 
 sparsepr_status validate(const sparsepr_shape* s, const sparsepr_params* p, Geom& g) {
@@ -260,7 +264,26 @@ sparsepr_status validate(const sparsepr_shape* s, const sparsepr_params* p, Geom
              (int64_t)g.M * (int64_t)N;
   g.nchunk_max = (N + kQTile - 1) / kQTile + g.CQt;
   g.nchunk_per_xcd = (g.nchunk_max + 7) / 8;
-  g.nsplit = (N + kProbeSplit - 1) / kProbeSplit;
+  g.rpad = (std::max(g.rk, g.rq) + 15) / 16 * 16;
+  {
+    // Key splits of the exact probe rows.  One split of 2048 keys per block
+    // leaves most of the chip idle for short sequences or few heads, so the
+    // splits halve until the launch has a round of blocks (256 CUs with 2
+    // fp32 or 6 bf16 blocks each) or the splits get as short as a few tiles
+    // per wave.  Their partials then go over the k-means operands, which only
+    // planning uses, as far as those hold them, so the workspace never grows.
+    const int64_t rows = (int64_t)g.BH * g.G * std::max(g.M, 1);
+    const int64_t blocks = (int64_t)g.BH * g.G * ((std::max(g.M, 1) + 63) / 64);
+    const int64_t scratch = (int64_t)2 * g.BH * NV * g.rpad * 2;
+    auto count = [&](int keys) { return (N + keys - 1) / keys; };
+    auto fits = [&](int keys) { return rows * count(keys) * (g.dv + 2) * 4 <= scratch; };
+    g.psplit = kProbeSplit;
+    const int64_t want = g.bf16 ? 1536 : 512;
+    const int least = g.bf16 ? 256 : 128;
+    while (blocks * count(g.psplit) < want && g.psplit > least && fits(g.psplit / 2)) g.psplit /= 2;
+    g.nsplit = count(g.psplit);
+    g.part_km = fits(g.psplit);
+  }
   {
     // Key segments of the sparse attention: each launch reads one slice of
     // the group-major K/V, sized to stay resident in one XCD's 4 MB L2 while
@@ -283,7 +306,6 @@ sparsepr_status validate(const sparsepr_shape* s, const sparsepr_params* p, Geom
     g.sel_cshift = (wb + cb <= 64 && wb < 64) ? wb : 0;
   }
   g.cmax = std::max(g.CKt, g.CQt);
-  g.rpad = (std::max(g.rk, g.rq) + 15) / 16 * 16;
   g.cpad = (std::max(g.CK, g.CQ) + 31) / 32 * 32;
   return SPARSEPR_OK;
 }

@@ -85,8 +85,8 @@ __device__ __forceinline__ bool get_work(const Geom& g, const AttnArgs& A, int b
     w.split = blockIdx.y;
     if (w.tile * 64 >= np) return false;
     w.nrows = min(64, np - w.tile * 64);
-    w.k0 = w.split * kProbeSplit;
-    w.nkeys = min(g.N - w.k0, kProbeSplit);
+    w.k0 = w.split * g.psplit;
+    w.nkeys = min(g.N - w.k0, g.psplit);
     return w.nkeys > 0;
   } else {
     w.tile = blockIdx.x;
@@ -599,29 +599,54 @@ __global__ __launch_bounds__(256) void k_permute_kv(Geom g, const void* k, const
   *(uint4*)(vperm + ((size_t)bh * g.N + p) * D + c * 8) = vv;
 }
 
-// fp32 variant (VALU): one thread per query row, 32-key tiles staged in LDS.
+// fp32 variant on the fp32 matrix instruction (v_mfma_f32_32x32x2_f32, fp32
+// products and accumulation: 157 TFLOP/s against 79 for unpacked vector FMAs).
+// A block of 4 waves owns up to 64 query rows (32 when the row tile is 32 or
+// the chunk is short): with 2 sets of 32 rows two waves share each set and
+// halve its keys, with one set four waves quarter them, every wave taking
+// each nparts-th 32-key tile; the partial (m, l, O) merge through LDS at the
+// end.  As in the bf16 kernel the scores are formed transposed, S^T = K Q^T,
+// so a lane's scores belong to one query and the probabilities feed
+// O^T += V^T P^T from registers.
+//  * Both contractions may take their terms in any order: lane (n, h) holds
+//    dims 8j + 4h + 0..3 of query n, so a key operand is one 16-byte load per
+//    four MFMAs; PV step i contracts the keys of score register i of both
+//    halves, and V^T row m of block db is value channel m * NDB + db, so one
+//    16-byte (D = 64: 8-byte) load of a value row serves every block.
+//  * Operands go straight from global memory to registers: a load feeds four
+//    64-cycle MFMAs, so the CU asks for 16 B/clk of K and V, far below what L1
+//    and L2 deliver, and there is no LDS tile, no barrier and no transposition.
+//    Loads run half a tile (2048 matrix cycles at D = 128) ahead.
+// One thread per row on vector FMAs in one-wave blocks, with K/V tiles staged
+// through LDS by scalar loads, took 9.97 ms for dense attention of 8 heads of
+// 2,442 rows at d = 64 (1.2 TFLOP/s); this kernel 0.204 ms (60 TFLOP/s; the
+// rest is the second round of blocks, 312 over 256 CUs, and exposed loads).
 template <int D, int MODE>
-__global__ __launch_bounds__(64) void k_attn_f32(Geom g, AttnArgs A) {
-  constexpr int KT = 32;
-  __shared__ float Ks[KT][D + 1];
-  __shared__ float Vs[KT][D + 1];
-  __shared__ int srcrow[KT];
-  const int bh = (MODE == MODE_PROBE) ? blockIdx.z : blockIdx.y;
+__global__ __launch_bounds__(256, 2) void k_attn_f32(Geom g, AttnArgs A) {
+  constexpr int KT = 32, NQ = D / 8, HQ = NQ / 2, NDB = D / 32;
+  constexpr int NREG = 16 * NDB;
+  typedef float fv __attribute__((ext_vector_type(NDB)));
+  __shared__ float red[3][NREG + 2][64];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 31, h = lane >> 5;
+  // block's query head j of K/V head bh; attend outputs are entry bq
+  const int bq = (MODE == MODE_SPARSE) ? blockIdx.y : blockIdx.z;
+  const int bh = bq % g.BH, jq = bq / g.BH;
   Work1 w;
   if (!get_work<MODE>(g, A, bh, w)) return;
-  const int tid = threadIdx.x;
-  const int64_t base = kv_base(g, bh), qbase = q_base(g, bh, g.gq);
+  const int64_t base = kv_base(g, bh), qbase = q_base(g, bh, jq);
   const float* Kp = (const float*)A.k + base;
   const float* Vp = (const float*)A.v + base;
   const float* Qp = (const float*)A.q + qbase;
-  const bool qvalid = tid < w.nrows;
-  const int qrow = qvalid ? row_of<MODE>(g, A, bh, w, tid) : 0;
-  float qv[D], o[D];
+  const int nsets = w.nrows > 32 ? 2 : 1, nparts = 4 / nsets;
+  const int set = nsets == 2 ? wv & 1 : 0, part = nsets == 2 ? wv >> 1 : wv;
+  const int qr = set * 32 + n;
+  const bool qvalid = qr < w.nrows;
+  const int qrow = row_of<MODE>(g, A, bh, w, qvalid ? qr : 0);
+  float4 q4[NQ];
 #pragma unroll
-  for (int c = 0; c < D; ++c) {
-    qv[c] = qvalid ? Qp[(int64_t)qrow * g.sn + c] : 0.f;
-    o[c] = 0.f;
-  }
+  for (int j = 0; j < NQ; ++j) q4[j] = *(const float4*)(Qp + (int64_t)qrow * g.sn + 8 * j + 4 * h);
   const int2* rg = nullptr;
   int nr = 0;
   if (MODE == MODE_SPARSE) {
@@ -629,61 +654,153 @@ __global__ __launch_bounds__(64) void k_attn_f32(Geom g, AttnArgs A) {
     nr = A.rng_cnt[(size_t)bh * g.CQt + w.a];
   }
   KeyCursor cur{0, 0};
+  // scores are scaled into base 2 with the softmax scale's own rounding
   const float scale = 1.f / sqrtf((float)D);
   const float l2e = 1.4426950408889634f;
   float m_run = -INFINITY, l_run = 0.f;
+  f32x16 O[NDB];
+#pragma unroll
+  for (int db = 0; db < NDB; ++db)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) O[db][i] = 0.f;
   const int ntile = (w.nkeys + KT - 1) / KT;
-  for (int t = 0; t < ntile; ++t) {
-    if (tid < KT) {
-      const int f = t * KT + tid;
-      srcrow[tid] = (f < w.nkeys) ? key_row<MODE>(g, A, bh, w, f, cur, rg, nr) : -1;
+  // row of key n of tile t; keys past the end repeat the last one and are masked
+  auto tile_row = [&](int t) {
+    return key_row<MODE>(g, A, bh, w, min(t * KT + n, w.nkeys - 1), cur, rg, nr);
+  };
+  float4 ka[HQ], kb[HQ];
+  fv va[8], vb[8];
+  auto load_k = [&](float4* dst, int row, int half) {
+    const float* src = Kp + (int64_t)row * g.sn + 4 * h + half * (HQ * 8);
+#pragma unroll
+    for (int j = 0; j < HQ; ++j) dst[j] = *(const float4*)(src + 8 * j);
+  };
+  auto load_v = [&](fv* dst, int row, int half) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int e = half * 8 + i;
+      const int r = __shfl(row, (e >> 2) * 8 + 4 * h + (e & 3));
+      dst[i] = *(const fv*)(Vp + (int64_t)r * g.sn + n * NDB);
     }
-    __syncthreads();
-    for (int i = tid; i < KT * D; i += 64) {
-      const int r = i / D, c = i % D;
-      const int src = srcrow[r];
-      Ks[r][c] = src >= 0 ? Kp[(int64_t)src * g.sn + c] : 0.f;
-      Vs[r][c] = src >= 0 ? Vp[(int64_t)src * g.sn + c] : 0.f;
+  };
+  f32x16 S;
+  auto scores = [&](const float4* kk, int half) {
+#pragma unroll
+    for (int j = 0; j < HQ; ++j) {
+      const float4 q = q4[half * HQ + j];
+      S = __builtin_amdgcn_mfma_f32_32x32x2f32(kk[j].x, q.x, S, 0, 0, 0);
+      S = __builtin_amdgcn_mfma_f32_32x32x2f32(kk[j].y, q.y, S, 0, 0, 0);
+      S = __builtin_amdgcn_mfma_f32_32x32x2f32(kk[j].z, q.z, S, 0, 0, 0);
+      S = __builtin_amdgcn_mfma_f32_32x32x2f32(kk[j].w, q.w, S, 0, 0, 0);
     }
-    __syncthreads();
-    const int kn = min(KT, w.nkeys - t * KT);
-    float s[KT];
+  };
+  auto pv = [&](const fv* vv, int half) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+        O[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vv[i][db], S[half * 8 + i], O[db], 0, 0, 0);
+  };
+  int row = 0, nrow = 0;
+  if (part < ntile) {
+    row = tile_row(part);
+    load_k(ka, row, 0);
+  }
+  for (int t = part; t < ntile; t += nparts) {
+    load_k(kb, row, 1);
+    const bool more = t + nparts < ntile;
+    if (more) nrow = tile_row(t + nparts);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) S[i] = 0.f;
+    scores(ka, 0);
+    load_v(va, row, 0);
+    scores(kb, 1);
+    load_v(vb, row, 1);
+    const int left = w.nkeys - t * KT;  // valid keys of this tile when below KT
     float mt = -INFINITY;
 #pragma unroll
-    for (int j = 0; j < KT; ++j) {
-      float acc = 0.f;
-#pragma unroll
-      for (int c = 0; c < D; ++c) acc = fmaf(qv[c], Ks[j][c], acc);
-      s[j] = (j < kn) ? acc * scale * l2e : -INFINITY;
-      mt = fmaxf(mt, s[j]);
+    for (int i = 0; i < 16; ++i) {
+      S[i] = S[i] * scale * l2e;
+      if (left < KT && (i >> 2) * 8 + 4 * h + (i & 3) >= left) S[i] = -INFINITY;
+      mt = fmaxf(mt, S[i]);
     }
-    const float m_new = fmaxf(m_run, mt);
-    const float alpha = exp2f(m_run - m_new);
-    m_run = m_new;
-    l_run *= alpha;
+    mt = pair_max(mt);
+    if (__any(mt > m_run)) {
+      const float m_new = fmaxf(m_run, mt);
+      const float alpha = exp2f(m_run - m_new);
+      m_run = m_new;
+      l_run *= alpha;
 #pragma unroll
-    for (int c = 0; c < D; ++c) o[c] *= alpha;
+      for (int db = 0; db < NDB; ++db)
 #pragma unroll
-    for (int j = 0; j < KT; ++j) {
-      const float p = exp2f(s[j] - m_new);
-      l_run += p;
-#pragma unroll
-      for (int c = 0; c < D; ++c) o[c] = fmaf(p, Vs[j][c], o[c]);
+        for (int i = 0; i < 16; ++i) O[db][i] *= alpha;
     }
-    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      S[i] = exp2f(S[i] - m_run);
+      l_run += S[i];
+    }
+    if (left < KT) {  // masked keys add nothing, whatever their row holds
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int db = 0; db < NDB; ++db) {
+          const int key = (i >> 2) * 8 + 4 * h + (i & 3);
+          if (key >= left) va[i][db] = 0.f;
+          if (key + 16 >= left) vb[i][db] = 0.f;
+        }
+    }
+    pv(va, 0);
+    if (more) load_k(ka, nrow, 0);
+    pv(vb, 1);
+    row = nrow;
   }
-  if (!qvalid) return;
+  float l_tot = pair_sum(l_run);
+  // merge the key parts of each row set into part 0
+  if (part > 0) {
+    float(*dst)[64] = red[nsets == 2 ? set : part - 1];
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) dst[db * 16 + i][lane] = O[db][i];
+    dst[NREG][lane] = m_run;
+    dst[NREG + 1][lane] = l_tot;
+  }
+  __syncthreads();
+  if (part > 0 || !qvalid) return;
+  for (int p = 1; p < nparts; ++p) {
+    const float(*src)[64] = red[nsets == 2 ? set : p - 1];
+    const float mp = src[NREG][lane], lp = src[NREG + 1][lane];
+    // a part without a tile holds (-inf, 0, 0); part 0 always has one
+    const float m_new = fmaxf(m_run, mp);
+    const float fa = exp2f(m_run - m_new), fb = exp2f(mp - m_new);
+    m_run = m_new;
+    l_tot = l_tot * fa + lp * fb;
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) O[db][i] = O[db][i] * fa + src[db * 16 + i][lane] * fb;
+  }
+  float* dst;
+  float inv = 1.f;
   if (MODE == MODE_PROBE) {
-    float* dst = A.part + (((size_t)bh * g.M + w.tile * 64 + tid) * g.nsplit + w.split) * (D + 2);
-    for (int c = 0; c < D; ++c) dst[c] = o[c];
-    dst[D] = m_run;
-    dst[D + 1] = l_run;
-  } else if (MODE == MODE_SPARSE) {
-    float* dst = A.osp + ((size_t)bh * g.N + qrow) * D;
-    for (int c = 0; c < D; ++c) dst[c] = o[c] / l_run;
+    dst = A.part + (((size_t)bq * g.M + w.tile * 64 + qr) * g.nsplit + w.split) * (D + 2);
+    if (h == 0) {
+      dst[D] = m_run;
+      dst[D + 1] = l_tot;
+    }
   } else {
-    float* dst = (float*)A.out + qbase + (int64_t)qrow * g.sn;
-    for (int c = 0; c < D; ++c) dst[c] = o[c] / l_run;
+    dst = (MODE == MODE_SPARSE) ? A.osp + ((size_t)bq * g.N + qrow) * D
+                                : (float*)A.out + qbase + (int64_t)qrow * g.sn;
+    inv = l_tot;
+  }
+  // register i of block db: value channel (8 (i / 4) + 4 h + i % 4) NDB + db
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    fv o;
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) o[db] = MODE == MODE_PROBE ? O[db][i] : O[db][i] / inv;
+    *(fv*)(dst + ((i >> 2) * 8 + 4 * h + (i & 3)) * NDB) = o;
   }
 }
 
@@ -758,9 +875,9 @@ static void attend_d(const Geom& g, const Work* wq, const void* q, const void* k
         g, k, v, wq[0].permk, wq[0].kperm, wq[0].vperm);
   }
   if (ev) (void)hipEventRecord(ev[0], s);
-  for (int j = 0; j < g.G; ++j) {
+  for (int j = 0; j < g.G && g.bf16; ++j) {
     const AttnArgs a = make_args(&wq[j], q, k, v, out);
-    if (g.bf16) {
+    {
       // one launch per key segment, so that all blocks in flight read the same
       // slice of K/V and it stays in L2
       for (int sg = 0; sg < g.nseg; ++sg) {
@@ -774,22 +891,21 @@ static void attend_d(const Geom& g, const Work* wq, const void* q, const void* k
                                            : dim3(8 * g.nchunk_per_xcd, g.BH);
         k_attn_mfma<D, MODE_SPARSE><<<grid, 128, 0, s>>>(gj(j), as);
       }
-    } else {
-      k_attn_f32<D, MODE_SPARSE><<<dim3(g.nchunk_max, g.BH), 64, 0, s>>>(gj(j), a);
     }
   }
+  // the fp32 kernels take every query head in one launch
+  const int BQ = g.BH * g.G;
+  const AttnArgs a0 = make_args(&wq[0], q, k, v, out);
+  if (!g.bf16) k_attn_f32<D, MODE_SPARSE><<<dim3(g.nchunk_max, BQ), 256, 0, s>>>(g, a0);
   if (ev) (void)hipEventRecord(ev[1], s);
   // the kernels below take all G * BH query heads in one launch (view of
   // query head 0, whose [G][BH] arrays continue with the other query heads)
-  const int BQ = g.BH * g.G;
   if (g.M > 0) {
-    for (int j = 0; j < g.G; ++j) {
+    for (int j = 0; j < g.G && g.bf16; ++j) {
       const AttnArgs a = make_args(&wq[j], q, k, v, out);
-      if (g.bf16)
-        k_attn_mfma<D, MODE_PROBE><<<gp, 128, 0, s>>>(gj(j), a);
-      else
-        k_attn_f32<D, MODE_PROBE><<<gp, 64, 0, s>>>(gj(j), a);
+      k_attn_mfma<D, MODE_PROBE><<<gp, 128, 0, s>>>(gj(j), a);
     }
+    if (!g.bf16) k_attn_f32<D, MODE_PROBE><<<dim3(gp.x, gp.y, BQ), 256, 0, s>>>(g, a0);
     k_probe_merge<<<dim3(g.M, BQ), 128, 0, s>>>(g, wq[0].part, wq[0].nprobes, wq[0].odp);
   }
   if (ev) (void)hipEventRecord(ev[2], s);
@@ -804,26 +920,28 @@ void launch_attend(const Geom& g, const Work* wq, const void* q, const void* k, 
     attend_d<128>(g, wq, q, k, v, out, s, ev);
 }
 
+template <int D>
+static void dense_d(const Geom& g, const AttnArgs& a, hipStream_t s) {
+  const int tiles = (g.N + 63) / 64;
+  if (!g.bf16) {
+    k_attn_f32<D, MODE_DENSE><<<dim3(tiles, 1, g.BH * g.G), 256, 0, s>>>(g, a);
+    return;
+  }
+  for (int j = 0; j < g.G; ++j) {  // every query head of each K/V head
+    Geom h = g;
+    h.gq = j;
+    k_attn_mfma<D, MODE_DENSE><<<dim3(tiles, g.BH), 128, 0, s>>>(h, a);
+  }
+}
+
 void launch_dense(const Geom& g, const void* q, const void* k, const void* v, void* out,
                   float* part, hipStream_t s) {
   (void)part;
   const AttnArgs a = make_args(nullptr, q, k, v, out);
-  const dim3 gd((g.N + 63) / 64, g.BH);
-  for (int j = 0; j < g.G; ++j) {  // every query head of each K/V head
-    Geom h = g;
-    h.gq = j;
-    if (g.d == 64) {
-      if (g.bf16)
-        k_attn_mfma<64, MODE_DENSE><<<gd, 128, 0, s>>>(h, a);
-      else
-        k_attn_f32<64, MODE_DENSE><<<gd, 64, 0, s>>>(h, a);
-    } else {
-      if (g.bf16)
-        k_attn_mfma<128, MODE_DENSE><<<gd, 128, 0, s>>>(h, a);
-      else
-        k_attn_f32<128, MODE_DENSE><<<gd, 64, 0, s>>>(h, a);
-    }
-  }
+  if (g.d == 64)
+    dense_d<64>(g, a, s);
+  else
+    dense_d<128>(g, a, s);
 }
 
 }  // namespace sparsepr

@@ -17,7 +17,8 @@ namespace sparsepr {
 constexpr int kQTile = 64;
 // Key tile of the attention kernels.
 constexpr int kKTile = 64;
-// Probe-row dense attention: keys per split.
+// Probe-row dense attention: most keys per split (fewer when that leaves the
+// chip idle).
 constexpr int kProbeSplit = 2048;
 // Tokens per block of the counting sort.
 constexpr int kSortBlock = 1024;
@@ -53,7 +54,8 @@ struct Geom {
   int64_t budget;         // video x video pair budget after the probe reservation
   int nchunk_max;         // attention work items per head (upper bound)
   int nchunk_per_xcd;     // ceil(nchunk_max / 8): chunks of one head per XCD
-  int nsplit;             // probe attention key splits
+  int psplit, nsplit;     // probe attention: keys per split, key splits
+  int part_km;            // the splits' partials live in the k-means operands
   int nseg;               // key segments of the sparse attention (one launch each)
   int nsort_blk;          // counting-sort blocks over NV rows
   int nsort_blk_full;     // counting-sort blocks over N rows
@@ -112,7 +114,7 @@ struct Work {
   uint16_t* vperm;    // [BH][N][dv] bf16 V in group-major order
   float* osp;         // [BH][N][dv]
   float* odp;         // [BH][M][dv]
-  float* part;        // [BH][M][nsplit][dv+2] split partials (o, m, l)
+  float* part;        // [BH][M][nsplit][dv+2] split partials (o, m, l); over km_xhi, km_xlo when part_km
   float* mlst;        // [BH][N][4] running (m, l_lo, l_hi) of the sparse attention between key segments
   float* fitv;        // [BH][3*dv] mu_x, s_x, mu_r
   float* fity;        // [BH][dv][r] B Psi

@@ -1,0 +1,55 @@
+"""Attention kernels at the edges of their tiles, key parts and key splits,
+against float64 rows on the CPU.  Tolerances are the parity tests': rel-L2
+1e-5 in fp32 (sums of d and n terms of 2^-24 each stay far below it) and 2e-2
+in bf16 (2^-9 of the rounded probabilities and output)."""
+import math
+
+import numpy as np
+import pytest
+
+from tests._common import medium, rel_l2
+from tests.test_gpu_parity import _replay, _run
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _dense64(q, k, v):
+    s = (q.double() @ k.double().transpose(-1, -2)) / math.sqrt(q.shape[-1])
+    return torch.softmax(s, -1) @ v.double()
+
+
+# one key; fewer keys than one tile, than one tile per key part; one and two
+# 32-row sets; ragged last tiles on either side of a tile edge
+@pytest.mark.parametrize("n", [1, 31, 33, 64, 97, 129, 256, 321, 1000])
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128)])
+@pytest.mark.parametrize("heads,kv", [(2, 2), (3, 1)])
+def test_dense_attention_edges(n, dtype, d, heads, kv):
+    from paper_2608_18484_amd import sparsepr as S
+    g = torch.Generator().manual_seed(n * 7 + d)
+    q, k, v = (torch.randn(2, h, n, d, generator=g) for h in (heads, kv, kv))
+    if dtype == "bf16":
+        q, k, v = (x.bfloat16() for x in (q, k, v))
+    got = S.dense_attention(q.cuda(), k.cuda(), v.cuda()).cpu().double()
+    rep = heads // kv
+    ref = _dense64(q, k.repeat_interleave(rep, 1), v.repeat_interleave(rep, 1))
+    assert rel_l2(got, ref) < (1e-5 if dtype == "f32" else 2e-2)
+
+
+# probe rows over key splits: the last split short, one and two tiles of
+# probes, more splits than the shortest split allows at this length
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("grid,m", [((1, 11, 13), 5), ((2, 23, 29), 33), ((3, 24, 31), 70)])
+def test_probe_rows_and_output_over_short_splits(orc, dtype, grid, m):
+    wl = medium(grid=grid, heads=2, dtype=dtype, n_probes=m)
+    r = _run(wl)
+    tol = 1e-5 if dtype == "f32" else 2e-2
+    for h in range(2):
+        ex = r["op"].export(h, fields=["labels_q", "labels_kv", "routes", "probes", "probe_weights",
+                                       "o_dense_probes", "o_sparse"])
+        q, k, v = (torch.from_numpy(r[x][0, h]) for x in "qkv")
+        ref = _dense64(q[ex["probes"].astype(np.int64)], k, v)
+        assert rel_l2(ex["o_dense_probes"], ref) < tol
+        out, _ = _replay(orc, r, ex, 0, h)
+        assert rel_l2(r["out"][0, h], out) < tol
