@@ -27,41 +27,45 @@ namespace sparsepr {
 // so Y = B_lambda Psi and the correction of row i is xbar_i Y Psi^T + mu_R.
 // ---------------------------------------------------------------------------
 
-// Per-head scratch of the fit: xbar [M][D], rbar [M][D], rbar*Psi [M][r],
-// rhs [D][r], w~ [M] (all double).
+// Per-head scratch of the fit: xbar [M][D], rbar [M][D], rhs [D][r], w~ [M]
+// (all double).
 struct FitScratch {
-  double *xb, *rb, *rp, *rhs, *wt;
+  double *xb, *rb, *rhs, *wt;
 };
 
 __device__ __forceinline__ FitScratch fit_scratch(const Geom& g, const Work& w, int bh) {
   const size_t D = g.dv, M = g.M, r = g.r;
-  double* base = w.fitscr + (size_t)bh * (2 * M * D + M * r + D * r + M);
+  double* base = w.fitscr + (size_t)bh * (2 * M * D + D * r + M);
   FitScratch f;
   f.xb = base;
   f.rb = f.xb + M * D;
-  f.rp = f.rb + M * D;
-  f.rhs = f.rp + M * r;
+  f.rhs = f.rb + M * D;
   f.wt = f.rhs + D * r;
   return f;
 }
 
 // Weighted statistics of the probes (eqs. app_normalized_weights ...
-// app_regression_weights): mu_x, mu_R, s_x, xbar, Rbar and w~.
+// app_regression_weights): mu_x, mu_R, s_x, xbar, Rbar and w~.  Thread
+// (c, s) takes column c of every (1024 / D)-th probe, so that a head's three
+// passes over its gathered probe rows are 16 short chains of loads at 128
+// probes instead of 128 (36 us with one thread per column).
 template <int D>
-__global__ __launch_bounds__(256) void k_fit_prep(Geom g, Work w) {
+__global__ __launch_bounds__(1024) void k_fit_prep(Geom g, Work w) {
+  constexpr int SP = 1024 / D;
   __shared__ double swsh;
+  __shared__ double sred[3][SP][D];
   const int bq = blockIdx.x, bh = bq % g.BH, tid = threadIdx.x;
   const int np = w.nprobes[bh];
   const int r = g.r;
   float* fv = w.fitv + (size_t)bq * 3 * D;
   float* Y = w.fity + (size_t)bq * D * r;
   float* Psi = w.fitpsi + (size_t)bq * D * r;
-  for (int i = tid; i < D * r; i += 256) {
+  for (int i = tid; i < D * r; i += 1024) {
     Y[i] = 0.f;
     Psi[i] = 0.f;
   }
   if (np == 0) {
-    for (int c = tid; c < D; c += 256) {
+    for (int c = tid; c < D; c += 1024) {
       fv[c] = 0.f;
       fv[D + c] = 1.f;
       fv[2 * D + c] = 0.f;
@@ -83,40 +87,57 @@ __global__ __launch_bounds__(256) void k_fit_prep(Geom g, Work w) {
   }
   __syncthreads();
   const double sw = swsh;
-  for (int p = tid; p < np; p += 256) f.wt[p] = (double)np * (double)pwt[p] / sw;
-  for (int c = tid; c < D; c += 256) {
-    double mx = 0.0, mr = 0.0;
+  for (int p = tid; p < np; p += 1024) f.wt[p] = (double)np * (double)pwt[p] / sw;
+  const int c = tid % D, st = tid / D;
+  // column sums over the strips, in strip order
+  auto total = [&](int which) {
+    double t = 0.0;
+#pragma unroll
+    for (int j = 0; j < SP; ++j) t += sred[which][j][c];
+    return t;
+  };
+  double mx = 0.0, mr = 0.0;
 #pragma unroll 8
-    for (int p = 0; p < np; ++p) {
-      const double al = (double)pwt[p] / sw;
-      const double x = osp[(size_t)pr[p] * D + c];
-      mx += al * x;
-      mr += al * ((double)odp[(size_t)p * D + c] - x);
-    }
-    double vx = 0.0;
+  for (int p = st; p < np; p += SP) {
+    const double al = (double)pwt[p] / sw;
+    const double x = osp[(size_t)pr[p] * D + c];
+    mx += al * x;
+    mr += al * ((double)odp[(size_t)p * D + c] - x);
+  }
+  sred[0][st][c] = mx;
+  sred[1][st][c] = mr;
+  __syncthreads();
+  mx = total(0);
+  mr = total(1);
+  double vx = 0.0;
 #pragma unroll 8
-    for (int p = 0; p < np; ++p) {
-      const double al = (double)pwt[p] / sw;
-      const double t = (double)osp[(size_t)pr[p] * D + c] - mx;
-      vx += al * t * t;
-    }
-    const double sx = sqrt(vx + (double)g.eps_x);
+  for (int p = st; p < np; p += SP) {
+    const double al = (double)pwt[p] / sw;
+    const double t = (double)osp[(size_t)pr[p] * D + c] - mx;
+    vx += al * t * t;
+  }
+  sred[2][st][c] = vx;
+  __syncthreads();
+  const double sx = sqrt(total(2) + (double)g.eps_x);
 #pragma unroll 8
-    for (int p = 0; p < np; ++p) {
-      const double x = osp[(size_t)pr[p] * D + c];
-      f.xb[(size_t)p * D + c] = (x - mx) / sx;
-      f.rb[(size_t)p * D + c] = ((double)odp[(size_t)p * D + c] - x) - mr;
-    }
+  for (int p = st; p < np; p += SP) {
+    const double x = osp[(size_t)pr[p] * D + c];
+    f.xb[(size_t)p * D + c] = (x - mx) / sx;
+    f.rb[(size_t)p * D + c] = ((double)odp[(size_t)p * D + c] - x) - mr;
+  }
+  if (st == 0) {
     fv[c] = (float)mx;
     fv[D + c] = (float)sx;
     fv[2 * D + c] = (float)mr;
   }
 }
 
-// The two weighted Gram matrices of the fit, one 32 x 32 tile per block:
+// The weighted Gram matrices of the fit, one 32 x 32 tile per block:
 // which = 0: H = Rbar^T W Rbar (its eigenvectors are the right singular
 // vectors of W^1/2 Rbar, eq. app_probe_residual_basis); which = 1:
-// S = xbar^T W xbar + lambda I (eq. app_ridge_closed_form).
+// S = xbar^T W xbar + lambda I (eq. app_ridge_closed_form); which = 2:
+// Rbar^T W xbar, so that the solve's right-hand side xbar^T W (Rbar Psi) is
+// one D x D x r product instead of two passes over the probes in its block.
 template <int D>
 __global__ __launch_bounds__(256) void k_fit_gram(Geom g, Work w) {
   constexpr int PB = 64;
@@ -127,7 +148,8 @@ __global__ __launch_bounds__(256) void k_fit_gram(Geom g, Work w) {
   if (np == 0) return;
   const int ti = blockIdx.x / (D / 32), tj = blockIdx.x % (D / 32);
   const FitScratch f = fit_scratch(g, w, bq);
-  const double* src = which == 0 ? f.rb : f.xb;
+  const double* srca = which == 1 ? f.xb : f.rb;
+  const double* srcb = which == 0 ? f.rb : f.xb;
   const int li = tid / 8, lj = (tid % 8) * 4;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
   for (int p0 = 0; p0 < np; p0 += PB) {
@@ -135,8 +157,8 @@ __global__ __launch_bounds__(256) void k_fit_gram(Geom g, Work w) {
     __syncthreads();
     for (int i = tid; i < pn * 32; i += 256) {
       const int p = i / 32, c = i % 32;
-      sa[p][c] = src[(size_t)(p0 + p) * D + ti * 32 + c];
-      sb[p][c] = src[(size_t)(p0 + p) * D + tj * 32 + c];
+      sa[p][c] = srca[(size_t)(p0 + p) * D + ti * 32 + c];
+      sb[p][c] = srcb[(size_t)(p0 + p) * D + tj * 32 + c];
     }
     for (int p = tid; p < pn; p += 256) swt[p] = f.wt[p0 + p];
     __syncthreads();
@@ -146,7 +168,7 @@ __global__ __launch_bounds__(256) void k_fit_gram(Geom g, Work w) {
       for (int e = 0; e < 4; ++e) acc[e] += a * sb[p][lj + e];
     }
   }
-  double* G = w.fitgram + ((size_t)bq * 2 + which) * D * D;
+  double* G = w.fitgram + ((size_t)bq * 3 + which) * D * D;
   const int i = ti * 32 + li;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
@@ -155,11 +177,107 @@ __global__ __launch_bounds__(256) void k_fit_gram(Geom g, Work w) {
   }
 }
 
+// S Y = B for a symmetric positive definite D x D S and r right-hand sides,
+// all double, by one block of 1024 threads: S = L diag(d) L^T by right-looking
+// elimination on the augmented matrix [S | B], which lives in registers
+// (thread = one column x one strip of D / 4 rows; rows i % 4 form a strip).
+// Step j publishes row j (double-buffered, so one barrier per step): by
+// symmetry it is also the column every row subtracts, and scaled by 1 / d_j it
+// is row j of L^T (kept in U, row stride D + 1) and of diag(d)^-1 L^-1 B (kept
+// in Z).  Then L^T Y = Z, one wave per right-hand side.  Returns false (Y
+// untouched) when a pivot is not positive.  The Cholesky factorisation with S
+// in LDS, two barriers per column and separate triangular solves took 256 us
+// of the block at D = 128.
+template <int D>
+__device__ __forceinline__ bool fit_spd_solve(const double* __restrict__ Sg, double* __restrict__ Z, int r, int rk, double* U,
+                              float* __restrict__ Y) {
+  constexpr int S = 4, NR = D / S, BK = 8, NB = NR / BK, LU = D + 1;
+  typedef double blk __attribute__((ext_vector_type(BK)));
+  __shared__ __attribute__((aligned(16))) double rowb[2][2][D];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int c = tid % D, strip = __builtin_amdgcn_readfirstlane(tid / D);
+  const bool rhs = strip >= S;
+  const int s = strip % S;
+  // waves whose columns are all beyond the right-hand sides only meet the
+  // barriers
+  const bool act = strip < 2 * S && (!rhs || __builtin_amdgcn_readfirstlane(c & ~63) < rk);
+  auto pos = [](int i) { return (i % S) * NR + i / S; };
+  blk a[NB];
+  if (act) {
+#pragma unroll
+    for (int bk = 0; bk < NB; ++bk)
+#pragma unroll
+      for (int e = 0; e < BK; ++e) {
+        const int i = s + S * (bk * BK + e);
+        a[bk][e] = rhs ? (c < rk ? Z[(size_t)i * r + c] : 0.0) : Sg[(size_t)i * D + c];
+      }
+    if (s == 0) rowb[0][rhs][rhs ? c : pos(c)] = a[0][0];
+  }
+  bool ok = true;
+  for (int j = 0; j < D; ++j) {
+    const int cur = j & 1;
+    __syncthreads();
+    const double* x = rowb[cur][0];
+    const double dj = x[pos(j)];
+    ok = ok && dj > 0.0;
+    if (act) {
+      const double f = rowb[cur][rhs][rhs ? c : pos(c)] / dj;
+      if (s == j % S) {
+        if (!rhs)
+          U[j * LU + c] = f;
+        else if (c < rk)
+          Z[(size_t)j * r + c] = f;
+      }
+      const double* xs = x + s * NR;
+#pragma unroll
+      for (int bk = 0; bk < NB; ++bk)
+        if (S * BK * (bk + 1) > j + 1) {
+#pragma unroll
+          for (int e = 0; e < BK; ++e) a[bk][e] -= xs[bk * BK + e] * f;
+        }
+      if (j + 1 < D && s == (j + 1) % S) {
+        const int u = (j + 1) / S;
+        double v = a[0][0];
+#pragma unroll
+        for (int bk = 0; bk < NB; ++bk)
+          if (u / BK == bk) {
+#pragma unroll
+            for (int e = 0; e < BK; ++e) v = u % BK == e ? a[bk][e] : v;
+          }
+        rowb[cur ^ 1][rhs][rhs ? c : pos(c)] = v;
+      }
+    }
+  }
+  __syncthreads();
+  if (!ok) return false;  // every thread saw the same pivots
+  constexpr int NU = D / 64;
+  for (int t = tid >> 6; t < rk; t += 1024 / 64) {
+    // lane l holds unknowns l, l + 64; each solved one is subtracted from
+    // the rows above it
+    double y[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) y[u] = Z[(size_t)(lane + 64 * u) * r + t];
+#pragma unroll 4
+    for (int j = D - 1; j > 0; --j) {
+      const double yj = tri_readlane(NU > 1 && j >= 64 ? y[NU - 1] : y[0], j & 63);
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        const int i = lane + 64 * u;
+        const double l = U[i * LU + j];
+        if (i < j) y[u] -= l * yj;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < NU; ++u) Y[(size_t)(lane + 64 * u) * r + t] = (float)y[u];
+  }
+  return true;
+}
+
 // Residual subspace and ridge solve, one block of 1024 threads per head:
 // Psi = leading r eigenvectors of H with sigma > 1e-6 sigma_1 (tridiagonal
-// solver in LDS, or cyclic Jacobi when its check fails); then
-// (xbar^T W xbar + lambda I) Y = xbar^T W (Rbar Psi) by Cholesky, so
-// Y = B_lambda Psi and the correction of row i is xbar_i Y Psi^T + mu_R.
+// solver, or cyclic Jacobi in LDS when its check fails); then
+// (xbar^T W xbar + lambda I) Y = xbar^T W (Rbar Psi), so Y = B_lambda Psi and
+// the correction of row i is xbar_i Y Psi^T + mu_R.
 // T is the eigensolver's precision.  Double A and V of a 128 x 128 problem do not
 // both fit in LDS; V (VG) then lives in the head's global scratch.
 template <int D, typename T>
@@ -167,12 +285,12 @@ __global__ __launch_bounds__(1024) void k_fit_solve(Geom g, Work w) {
   constexpr int LD = D + 1, LV = jacobi_vt_ld<D>();
   constexpr bool VG = (size_t)D * (LD + LV) * sizeof(T) > 140 * 1024;
   constexpr size_t JAC = (size_t)D * (LD + (VG ? 0 : LV)) * sizeof(T),
-                   CHOL = (size_t)D * D * sizeof(double);
+                   CHOL = (size_t)D * LD * sizeof(double);
   __shared__ __attribute__((aligned(16))) unsigned char smem[JAC > CHOL ? JAC : CHOL];
   __shared__ JacobiRot<T> rot[D / 2];
   __shared__ TriWork<D, T, 1024> tw;
   __shared__ int order[D];
-  __shared__ int flag, rank_s, fail;
+  __shared__ int flag, rank_s;
   const int bq = blockIdx.x, bh = bq % g.BH, tid = threadIdx.x;
   const int np = w.nprobes[bh];
   if (np == 0) return;
@@ -180,24 +298,20 @@ __global__ __launch_bounds__(1024) void k_fit_solve(Geom g, Work w) {
   float* Y = w.fity + (size_t)bq * D * r;
   float* Psi = w.fitpsi + (size_t)bq * D * r;
   const FitScratch f = fit_scratch(g, w, bq);
-  const double* H = w.fitgram + ((size_t)bq * 2 + 0) * D * D;
-  const double* Sg = w.fitgram + ((size_t)bq * 2 + 1) * D * D;
+  const double* H = w.fitgram + (size_t)bq * 3 * D * D;
+  const double* Sg = H + D * D;
+  const double* C = Sg + D * D;
   T* Am = (T*)smem;
   T* Vm = VG ? (T*)(w.fitvec + (size_t)bq * D * LV) : Am + D * LD;  // transposed (jacobi_eig_lds)
   if (g.ridge_only) {
     // ridge estimator alone (Table probe_estimator_ablation): Psi = I
     for (int e = tid; e < D * D; e += 1024) Vm[(e / D) * LV + (e % D)] = (e / D == e % D) ? T(1) : T(0);
     if (tid < D) order[tid] = tid;
-    if (tid == 0) {
-      rank_s = D;
-      fail = 0;
-    }
+    if (tid == 0) rank_s = D;
     __syncthreads();
   } else {
-    for (int e = tid; e < D * D; e += 1024) Am[(e / D) * LD + (e % D)] = (T)H[e];
-    __syncthreads();
-    tri_reduce<D, T, 1024>(Am, tw);
-    tri_eigvals<D, T, 1024>(tw);
+    tri_reduce_reg<D, T, 1024>([&](int e) { return (T)H[e]; }, Am, tw);
+    tri_eigvals<D, T, 1024>(tw, r + 1);
     if (tid == 0) {
       // rank: the leading t < r with sigma_t > 1e-6 sigma_1.  In double the
       // float eigenvalues of the multisection cannot place an eigenvalue
@@ -217,12 +331,11 @@ __global__ __launch_bounds__(1024) void k_fit_solve(Geom g, Work w) {
           break;
       }
       rank_s = amb ? -1 : rk;
-      fail = 0;
     }
     __syncthreads();
-    if (rank_s >= 0) tri_vectors<D, T, 1024>(tw, Vm, LV, rank_s, w.eigscr + (size_t)bq * 4 * D * D);
+    if (rank_s >= 0) tri_vectors<D, false>(tw, Vm, LV, rank_s, w.eigscr + (size_t)bq * 2 * D * D, (double*)nullptr);
     if (rank_s >= 0 && tw.ok) {
-      tri_back<D, T, 1024>(Am, tw, Vm, LV, rank_s);
+      tri_back_rows<D, T, 1024>(Am, tw, Vm, LV, rank_s);
       if (tid < D) order[tid] = tid;
     } else {
       if (tid == 0)
@@ -264,114 +377,32 @@ __global__ __launch_bounds__(1024) void k_fit_solve(Geom g, Work w) {
     const int row = i / rk, t = i % rk;
     Psi[row * r + t] = (float)Vm[order[t] * LV + row];
   }
-  for (int i = tid; i < np * rk; i += 1024) {
-    const int p = i / rk, t = i % rk;
-    double acc = 0.0;
-    for (int c = 0; c < D; ++c) acc += f.rb[(size_t)p * D + c] * (double)Vm[order[t] * LV + c];
-    f.rp[(size_t)p * r + t] = acc;
-  }
-  __syncthreads();
-  // rhs = xbar^T W (Rbar Psi): the probe weights and Rbar Psi are staged in
-  // the LDS (free again here) when they fit; each sum runs over the probes in
-  // order either way
-  double* rps = (double*)smem;  // [np][rk], then [np] weights
-  const bool staged = (size_t)np * (rk + 1) * sizeof(double) <= sizeof(smem);
-  if (staged) {
-    for (int i = tid; i < np * rk; i += 1024) rps[i] = f.rp[(size_t)(i / rk) * r + i % rk];
-    for (int p = tid; p < np; p += 1024) rps[np * rk + p] = f.wt[p];
-  }
-  __syncthreads();
-  for (int i = tid; i < D * rk; i += 1024) {
-    const int c = i / rk, t = i % rk;
-    double acc = 0.0;
-    if (staged) {
-#pragma unroll 8
-      for (int p = 0; p < np; ++p) acc += rps[np * rk + p] * f.xb[(size_t)p * D + c] * rps[p * rk + t];
-    } else {
-      for (int p = 0; p < np; ++p) acc += f.wt[p] * f.xb[(size_t)p * D + c] * f.rp[(size_t)p * r + t];
-    }
-    f.rhs[(size_t)c * r + t] = acc;
-  }
-  // Cholesky S = L L^T in LDS (double), right-looking: at step j every
-  // thread takes sqrt(S_jj) itself, scales its part of column j, and after
-  // one barrier updates the lower triangle of the trailing block by column
-  // (k = tid % D) and rows (i = j + 1 + tid / D + NT/D * u, i >= k).
-  double* S = (double*)smem;
-  __syncthreads();
-  for (int e = tid; e < D * D; e += 1024) S[e] = Sg[e];
-  __syncthreads();
+  // rhs = (xbar^T W Rbar) Psi: thread (c, g) takes row c of every
+  // (1024 / D)-th direction, two at a time
   {
-    constexpr int RS = 1024 / D;  // row strips
-    const int kc = tid % D, i0 = tid / D;
-    for (int j = 0; j < D; ++j) {
-      const double dj = S[j * D + j];
-      const double ljj = dj > 0.0 ? sqrt(dj) : 1.0;
-      for (int i = j + 1 + tid; i < D; i += 1024) S[i * D + j] /= ljj;
-      __syncthreads();
-      if (tid == 0) {
-        if (!(dj > 0.0)) fail = 1;
-        S[j * D + j] = ljj;
+    constexpr int GT = 1024 / D;
+    const int c = tid % D;
+    for (int t0 = tid / D; t0 < rk; t0 += 2 * GT) {
+      const bool two = t0 + GT < rk;
+      const T* v0 = Vm + order[t0] * LV;
+      const T* v1 = Vm + order[two ? t0 + GT : t0] * LV;
+      double a0 = 0.0, a1 = 0.0;
+#pragma unroll 16
+      for (int e = 0; e < D; ++e) {
+        const double x = C[(size_t)e * D + c];
+        a0 += x * (double)v0[e];
+        a1 += x * (double)v1[e];
       }
-      if (kc > j) {
-        const double lk = S[kc * D + j];
-        for (int i = j + 1 + i0; i < D; i += RS)
-          if (i >= kc) S[i * D + kc] -= S[i * D + j] * lk;
-      }
-      __syncthreads();
+      f.rhs[(size_t)c * r + t0] = a0;
+      if (two) f.rhs[(size_t)c * r + t0 + GT] = a1;
     }
-  }
-  // L^T into the strict upper triangle (S[i][k] = L[k][i], k > i), so that
-  // both triangular solves below read rows
-  for (int e = tid; e < D * D; e += 1024) {
-    const int i = e / D, k = e % D;
-    if (k > i) S[i * D + k] = S[k * D + i];
   }
   __syncthreads();
-  // L L^T Y = rhs: wave t solves right-hand side t, lane l holding rows
-  // l, l + 64, ... in registers.  Both solves subtract each solved unknown
-  // from the rows still open: L y = b from the first row down (row i of the
-  // upper copy holds column i of L), then L^T x = y from the last row up
-  // (row i of L).
-  {
-    constexpr int U = (D + 63) / 64;
-    static_assert(U <= 2, "rows per lane");
-    const int lane = tid & 63;
-    for (int wv = tid >> 6; wv < rk && !fail; wv += 1024 / 64) {
-      double y[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int i = lane + 64 * u;
-        y[u] = i < D ? f.rhs[(size_t)i * r + wv] : 0.0;
-      }
-      for (int i = 0; i < D; ++i) {
-        const double yi = tri_readlane(U > 1 && i >= 64 ? y[U - 1] : y[0], i & 63) / S[i * D + i];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int k = lane + 64 * u;
-          if (k > i && k < D) y[u] -= S[i * D + k] * yi;
-          if (k == i) y[u] = yi;
-        }
-      }
-      for (int i = D - 1; i >= 0; --i) {
-        const double xi = tri_readlane(U > 1 && i >= 64 ? y[U - 1] : y[0], i & 63) / S[i * D + i];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int k = lane + 64 * u;
-          if (k < i) y[u] -= S[i * D + k] * xi;
-          if (k == i) y[u] = xi;
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int i = lane + 64 * u;
-        if (i < D) Y[i * r + wv] = (float)y[u];
-      }
-    }
-  }
+  const bool ok = fit_spd_solve<D>(Sg, f.rhs, r, rk, (double*)smem, Y);
   if (tid == 0) {
     int64_t* st = w.stats + (size_t)bh * 16;
     st[ST_FIT_RANK] = rk;
-    if (fail) atomicOr((unsigned long long*)&st[ST_FLAGS], (unsigned long long)SPARSEPR_FLAG_FIT_NOT_PD);
+    if (!ok) atomicOr((unsigned long long*)&st[ST_FLAGS], (unsigned long long)SPARSEPR_FLAG_FIT_NOT_PD);
   }
 }
 
@@ -523,8 +554,8 @@ static void fit_d(const Geom& g, const Work& w0, void* out, hipStream_t s, hipEv
   // all G * BH query heads in one launch (view of query head 0, whose [G][BH]
   // arrays continue with the other query heads)
   const int BQ = g.BH * g.G;
-  k_fit_prep<D><<<BQ, 256, 0, s>>>(g, w0);
-  k_fit_gram<D><<<dim3((D / 32) * (D / 32), 2, BQ), 256, 0, s>>>(g, w0);
+  k_fit_prep<D><<<BQ, 1024, 0, s>>>(g, w0);
+  k_fit_gram<D><<<dim3((D / 32) * (D / 32), 3, BQ), 256, 0, s>>>(g, w0);
   // float inputs (whose outputs are held to float rounding) get the double
   // solve; bf16 inputs the float one
   if (D <= 64 || !g.bf16)

@@ -129,11 +129,13 @@ __device__ void eig_order(const T* A, int* order) {
 // the block reloads the matrix and solves it by cyclic Jacobi instead.
 template <int D>
 __global__ __launch_bounds__(1024) void k_eig_basis(const double* gram, int r, float tau, float* F,
-                                                    float* evals, double* scr, int64_t* stats) {
+                                                    float* evals, double* scr, double* rat,
+                                                    int64_t* stats) {
   using T = typename std::conditional<D <= 64, double, float>::type;
   constexpr int LD = D + 1;
   constexpr int LV = jacobi_vt_ld<D>();
-  __shared__ T A[D * LD];
+  // the reflectors, or the matrix of the Jacobi solve
+  __shared__ __attribute__((aligned(16))) T A[D * LD];
   __shared__ __attribute__((aligned(16))) T VT[D * LV];
   __shared__ JacobiRot<T> rot[D / 2];
   __shared__ TriWork<D, T, 1024> tw;
@@ -143,10 +145,15 @@ __global__ __launch_bounds__(1024) void k_eig_basis(const double* gram, int r, f
   __shared__ double meanv;
   const int bh = blockIdx.x, tid = threadIdx.x;
   const double* G = gram + (size_t)bh * D * D;
-  for (int i = tid; i < D * D; i += blockDim.x) A[(i / D) * LD + (i % D)] = (T)G[i];
-  __syncthreads();
-  tri_reduce<D, T, 1024>(A, tw);
-  tri_eigvals<D, T, 1024>(tw);
+  constexpr bool SEQ = sizeof(T) == 4;  // see tridiag_eig.hpp
+  if constexpr (SEQ) {
+    for (int i = tid; i < D * D; i += blockDim.x) A[(i / D) * LD + (i % D)] = (T)G[i];
+    __syncthreads();
+    tri_reduce<D, T, 1024>(A, tw);
+  } else {
+    tri_reduce_reg<D, T, 1024>([&](int e) { return (T)G[e]; }, A, tw);
+  }
+  tri_eigvals<D, T, 1024>(tw, r + 1);
   if (tid == 0) {
     const float l1 = tw.lamf[0];
     int n = 0;
@@ -154,13 +161,15 @@ __global__ __launch_bounds__(1024) void k_eig_basis(const double* gram, int r, f
     nvec = n;
   }
   __syncthreads();
-  tri_vectors<D, T, 1024>(tw, VT, LV, nvec, scr + (size_t)bh * 4 * D * D);
+  tri_vectors<D, SEQ>(tw, VT, LV, nvec, scr + (size_t)bh * 2 * D * D, rat + (size_t)bh * 3 * D * D);
   if (tw.ok) {
-    tri_back<D, T, 1024>(A, tw, VT, LV, nvec);
+    if constexpr (SEQ)
+      tri_back<D, T, 1024>(A, tw, VT, LV, nvec);
+    else
+      tri_back_rows<D, T, 1024>(A, tw, VT, LV, nvec);
     if (tid < D) {
       order[tid] = tid;
-      lam[tid] = tid < nvec ? tw.lamv[tid]
-                            : ((tw.lamf[0] > 0.f && tw.lamf[tid] >= tau * tw.lamf[0]) ? (double)tw.lamf[tid] : 0.0);
+      lam[tid] = tid < nvec ? tw.lamv[tid] : 0.0;
     }
   } else {
     if (tid == 0)
@@ -2541,7 +2550,8 @@ static void plan_d(const Geom& g, const Work& w, const void* q, const void* k, h
     k_identity_basis<<<BH, 256, 0, s>>>(w.fk, w.gram_k, w.evals_k, D);
   } else {
     k_key_metric<D><<<dim3(D / 16, BH), 256, 0, s>>>(q, g, w.gram_k);
-    k_eig_basis<D><<<BH, 1024, 0, s>>>(w.gram_k, g.rk, 1e-6f, w.fk, w.evals_k, w.eigscr, w.stats);
+    k_eig_basis<D><<<BH, 1024, 0, s>>>(w.gram_k, g.rk, 1e-6f, w.fk, w.evals_k, w.eigscr, w.fitgram,
+                                       w.stats);
   }
   project<D>(g, w, k, w.fk, g.rk, 0, 0, 0.f, w.phik, s);
   KmArgs ak{w.phik, w.centk, w.labk, w.permk, w.offk, w.blkhist, w.kmstate, g.NV, g.ntext, g.N,
@@ -2553,7 +2563,8 @@ static void plan_d(const Geom& g, const Work& w, const void* q, const void* k, h
                                                          w.kbar, 0);
   if (g.partition == SPARSEPR_PARTITION_RESPONSE) {
     k_query_metric<D><<<dim3(D * D / 2048, BH), 256, 0, s>>>(w.kbar, w.offk, g, w.gram_q);
-    k_eig_basis<D><<<BH, 1024, 0, s>>>(w.gram_q, g.rq, 1e-6f, w.fq, w.evals_q, w.eigscr, w.stats);
+    k_eig_basis<D><<<BH, 1024, 0, s>>>(w.gram_q, g.rq, 1e-6f, w.fq, w.evals_q, w.eigscr, w.fitgram,
+                                       w.stats);
     project<D>(g, w, q, w.fq, g.rq, 1, 1, g.eps_q, w.phiq, s);
   } else {
     // semantic query groups: k-means on the raw queries

@@ -2,27 +2,44 @@
 // probe-residual basis (App. A.3 eq. app_probe_residual_basis), one block of
 // NT threads per D x D matrix, in four stages:
 //
-//  1. tri_reduce: Householder reduction to tridiagonal form in LDS,
-//     A = Q T Q^T with Q = H_0 H_1 ... H_{D-3}; reflector k is stored in
-//     column k below the subdiagonal, its scale in beta[k].
-//  2. tri_eigvals: every eigenvalue of T by multisection of its Sturm counts
-//     in float (NT / D threads per eigenvalue, each counting at one point of
-//     the current bracket), sorted descending.
+//  1. Householder reduction to tridiagonal form, A = Q T Q^T with
+//     Q = H_0 H_1 ... H_{D-3}, beta[k] the scale of reflector k: tri_reduce
+//     (A in LDS, reflectors below its subdiagonal) or tri_reduce_reg (A in
+//     registers, reflectors in the rows of V).
+//  2. tri_eigvals: the leading eigenvalues of T by multisection of its Sturm
+//     counts in float (8 or 16 threads per eigenvalue, each counting at one
+//     point of the current bracket), descending.
 //  3. tri_vectors: for the leading nvec eigenvalues, the twisted
 //     factorisation of T - lambda I in double (stationary and progressive
 //     pivot chains, each vector's two chains in different waves; twist index
-//     at the smallest |gamma|, found by a group of 8 lanes per vector), one
-//     Rayleigh-quotient correction lambda += gamma / |z|^2, a second
-//     factorisation and the twisted vector (its two sides swept by two lanes
-//     of the group).  The vectors' tridiagonal residuals and mutual
-//     orthogonality are then checked; ok = 0 reports a numerically repeated
-//     eigenvalue (whose twisted vectors coincide) so that the caller can use
-//     its Jacobi solver instead.
-//  4. tri_back: the vectors are multiplied by Q (reflectors applied last to
-//     first), each by a group of NT / D lanes of one wave with no barriers.
+//     at the smallest |gamma|, found by a group of 8 lanes per vector) with
+//     Rayleigh-quotient corrections lambda += gamma / |z|^2, then the twisted
+//     vector.  The vectors' tridiagonal residuals and mutual orthogonality
+//     are then checked; ok = 0 reports a numerically repeated eigenvalue
+//     (whose twisted vectors coincide) so that the caller can use its Jacobi
+//     solver instead.
+//  4. tri_back, tri_back_rows: the vectors are multiplied by Q (reflectors
+//     applied last to first), each by a group of lanes of one wave with no
+//     barriers.
 //
-// The reduction moves O(D^3) words through LDS once, against the O(D^3) per
-// sweep of cyclic Jacobi; the tridiagonal stages are O(D^2).
+// Every stage is a serial chain of one block, so latency is what counts:
+//  * tri_reduce takes four barriers per column and one wave forms each
+//    reflector: 231 us at D = 128 (1.8 us per column); tri_reduce_reg two
+//    barriers, 138 us in float and 206 in double (D = 64, double: 65 us);
+//  * the vectors' products, one lane per side and three sweeps over pivots
+//    in global memory, were two thirds of stage 3 (97 us for 64 vectors at
+//    D = 128); formed by all 8 lanes and kept in registers, stage 3 takes 51;
+//  * with a fixed two Rayleigh passes, vectors of eigenvalues closer than
+//    about 1e-3 of the largest kept more than 1e-9 of their neighbours, so
+//    that double solves fell back to Jacobi on most inputs (0.93-1.0 ms a
+//    solve at D = 64, 3 ms at D = 128).  The passes now go on until the
+//    correction is small against the gap to the neighbouring eigenvalues
+//    (their quotient bounds the vector's share of them).
+//
+// The float bases of D = 128 keep the sequential forms (tri_reduce, SEQ
+// vectors, tri_back): thousands of k-means decisions per head turn on their
+// last bits, and a basis with other roundings, however exact, regroups a few
+// rows of the largest calls.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <float.h>
@@ -32,16 +49,36 @@ namespace sparsepr {
 
 template <int D, typename T, int NT = 1024>
 struct TriWork {
-  double d[D], e[D], e2[D];  // diagonal, subdiagonal e[i] = T[i+1][i], e^2; e[D-1] = 0
+  // tri_reduce_reg: waves holding the matrix.  At D = 128 two per SIMD (one
+  // wave alone issues an instruction only every other slot: 186 us with 4
+  // waves, 138 with 8); at D = 64 each wave has little to do beside the
+  // scalars that every wave forms (65 us with 4, 70 with 8).  S strips of NR
+  // rows (row i belongs to strip i % S).
+  static constexpr int RW = D == 128 ? 8 : 4;
+  static constexpr int S = RW * 64 / D, NR = D / S;
+  static_assert(RW * 64 <= NT && S >= 2, "thread mapping");
+  double d[D], e[D];         // diagonal, subdiagonal e[i] = T[i+1][i]; e[D-1] = 0
   float2 de[D];              // float (d[i], e2[i-1]) for the Sturm counts
-  float lamf[D];             // eigenvalues from multisection, descending
+  float lamf[D];             // leading eigenvalues from multisection, descending
   double lamv[D];            // Rayleigh-corrected eigenvalues of the vectors
   T beta[D];                 // reflector scales
-  T hv[D], hw[D];            // reflector v and w = p - K v of the current step
-  T part[NT / D][D];         // partial sums of p = A v
+  union {
+    struct {  // tri_reduce_reg: rows k and k + 1 of the current step (double-
+              // buffered), partial sums of A x and each wave's w = p - K v,
+              // all in strip order
+      alignas(16) T xb[2][D];
+      alignas(16) T yb[2][D];
+      alignas(16) T part[S][D];
+      alignas(16) T ww[RW][D];
+    };
+    struct {  // tri_reduce: reflector v, w = p - K v, partial sums of p = A v
+      T hv[D], hw[D];
+      T lpart[NT / D][D];
+    };
+  };
   float glo, ghi, fnorm;
   double pivd;
-  int ok;
+  int ok, again;
 };
 
 // Lane exchanges by DPP (no LDS round trip): quad_perm [1,0,3,2] and
@@ -142,7 +179,7 @@ __device__ void tri_reduce(T* A, TriWork<D, T, NT>& tw) {
     if (c > k) {
       T acc = 0;
       for (int j = k + 1 + s; j < D; j += S) acc += A[j * LD + c] * tw.hv[j];
-      tw.part[s][c] = acc;
+      tw.lpart[s][c] = acc;
     }
     __syncthreads();
     if (wid == 0) {
@@ -154,7 +191,7 @@ __device__ void tri_reduce(T* A, TriWork<D, T, NT>& tw) {
         if (i < D) {
           T acc = 0;
 #pragma unroll
-          for (int q = 0; q < S; ++q) acc += tw.part[q][i];
+          for (int q = 0; q < S; ++q) acc += tw.lpart[q][i];
           p[u] = b * acc;
           pv += p[u] * tw.hv[i];
         }
@@ -181,6 +218,153 @@ __device__ void tri_reduce(T* A, TriWork<D, T, NT>& tw) {
   __syncthreads();
 }
 
+// Square root and reciprocal of the reflector's scalars: in float the
+// hardware's root (about 1 ulp: it only places alpha) and a refined
+// reciprocal.
+__device__ __forceinline__ float tri_sqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
+__device__ __forceinline__ double tri_sqrt(double x) { return sqrt(x); }
+__device__ __forceinline__ float tri_inv(float x) {
+  const float r = __builtin_amdgcn_rcpf(x);
+  return fmaf(fmaf(-x, r, 1.f), r, r);
+}
+__device__ __forceinline__ double tri_inv(double x) { return 1.0 / x; }
+
+// Stage 1 with the matrix in registers.  load(e): element e of the D x D symmetric matrix (row-major).
+// Step k takes x = row k right of the diagonal to alpha e_1 by H = I - beta
+// v v^T, v = x + (v0 - x0) e_{k+1}, and applies A <- A - v w^T - w v^T,
+// w = p - K v, p = beta A v, K = beta p.v / 2.  A x is summed while every
+// wave forms the reflector's scalars, A v = A x + (v0 - x0) A e_{k+1} taking
+// the difference from row k + 1 (y).  Each wave then forms w for itself, and
+// the strips owning rows k + 1 and k + 2 publish them for the next step: two
+// barriers per step.  Rows and columns up to k are left alone by zeros in
+// x and w.  Waves beyond RW only meet the barriers.
+template <int D, typename T, int NT, class Load>
+__device__ void tri_reduce_reg(Load load, T* V, TriWork<D, T, NT>& tw) {
+  using W = TriWork<D, T, NT>;
+  constexpr int RW = W::RW, S = W::S, NR = W::NR, U = D / 64;
+  constexpr int BK = 8, NB = NR / BK;
+  static_assert(NR % BK == 0, "row blocks");
+  typedef T blk __attribute__((ext_vector_type(BK)));
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool red = wid < RW;
+  const int c = tid % D, s = __builtin_amdgcn_readfirstlane(tid / D) % S;
+  auto pos = [](int i) { return (i % S) * NR + i / S; };
+  auto row_at = [](int q) { return q / NR + S * (q % NR); };
+  blk a[NB];
+  // register of row s + S u (u is wave-uniform): selects inside its block
+  // (a dynamic index would put the matrix in scratch memory)
+  auto pick = [&](int u) {
+    T r = a[0][0];
+#pragma unroll
+    for (int bk = 0; bk < NB; ++bk)
+      if (u / BK == bk) {
+#pragma unroll
+        for (int e = 0; e < BK; ++e) r = u % BK == e ? a[bk][e] : r;
+      }
+    return r;
+  };
+  if (red) {
+#pragma unroll
+    for (int bk = 0; bk < NB; ++bk)
+#pragma unroll
+      for (int e = 0; e < BK; ++e) a[bk][e] = load((s + S * (bk * BK + e)) * D + c);
+    if (s == 0) {
+      tw.xb[0][pos(c)] = c > 0 ? a[0][0] : T(0);
+      if (c == 0) tw.d[0] = (double)a[0][0];
+    } else if (s == 1) {
+      tw.yb[0][pos(c)] = a[0][0];
+    }
+  }
+  __syncthreads();
+  for (int kk = 0; kk < D - 1; ++kk) {
+    const int k = __builtin_amdgcn_readfirstlane(kk);  // keeps every test on it scalar
+    const int cur = k & 1;
+    const T* x = tw.xb[cur];
+    const T* xs = x + s * NR;
+    T xl[U], alpha = 0, b = 0, v0 = 0, x0 = 0;
+    if (red) {
+      T st = 0;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int q = lane + 64 * u;
+        xl[u] = x[q];
+        if (row_at(q) != k + 1) st += xl[u] * xl[u];
+      }
+      x0 = x[pos(k + 1)];
+      T acc[2] = {0, 0};
+#pragma unroll
+      for (int bk = 0; bk < NB; ++bk)
+        if (S * BK * (bk + 1) > k + 1) {
+#pragma unroll
+          for (int e = 0; e < BK; ++e) acc[e & 1] = fma(a[bk][e], xs[bk * BK + e], acc[e & 1]);
+        }
+      tw.part[s][pos(c)] = acc[0] + acc[1];
+      st = tri_wave_sum(st);
+      alpha = x0;
+      v0 = x0;
+      if (st > T(0)) {
+        const T nrm = tri_sqrt(fma(x0, x0, st));
+        alpha = x0 >= T(0) ? -nrm : nrm;
+        v0 = x0 - alpha;
+        // beta = 2 / v.v of the rounded v keeps H orthogonal to rounding
+        b = tri_inv(T(0.5) * fma(v0, v0, st));
+      }
+    }
+    __syncthreads();
+    if (red) {
+      const T dl = v0 - x0;
+      T p[U], vl[U], pv = 0;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int q = lane + 64 * u, i = row_at(q);
+        T t = dl * tw.yb[cur][q];
+#pragma unroll
+        for (int j = 0; j < S; ++j) t += tw.part[j][q];
+        p[u] = i > k ? b * t : T(0);
+        vl[u] = i == k + 1 ? v0 : xl[u];
+        pv += p[u] * vl[u];
+      }
+      const T K = T(0.5) * b * tri_wave_sum(pv);
+      T* ww = tw.ww[wid];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int q = lane + 64 * u;
+        ww[q] = p[u] - K * vl[u];
+        if (wid == 0) V[k * D + row_at(q)] = vl[u];
+      }
+      if (tid == 0) {
+        tw.beta[k] = b;
+        tw.e[k] = (double)alpha;
+      }
+      // ww is this wave's own: its reads only have to follow its writes
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      const T wc = ww[pos(c)], vc = c == k + 1 ? v0 : x[pos(c)];
+      const T* ws = ww + s * NR;
+#pragma unroll
+      for (int bk = 0; bk < NB; ++bk)
+        if (S * BK * (bk + 1) > k + 1) {
+#pragma unroll
+          for (int e = 0; e < BK; ++e)
+            a[bk][e] = fma(-xs[bk * BK + e], wc, fma(-ws[bk * BK + e], vc, a[bk][e]));
+        }
+      if (s == (k + 1) % S) {
+        // row k + 1 took x0 where its reflector entry is v0
+        const T r = pick((k + 1) / S) - dl * wc;
+        tw.xb[cur ^ 1][pos(c)] = c > k + 1 ? r : T(0);
+        if (c == k + 1) tw.d[k + 1] = (double)r;
+      } else if (s == (k + 2) % S && k + 2 < D) {
+        tw.yb[cur ^ 1][pos(c)] = pick((k + 2) / S);
+      }
+    }
+    __syncthreads();
+  }
+  if (tid == 0) tw.e[D - 1] = 0.0;
+  __syncthreads();
+}
+
 // Number of eigenvalues of T below x (float Sturm sequence).  Every e^2 is
 // at least FLT_MIN, so a zero pivot gives an infinite next pivot (never a
 // NaN) and the sequence continues from the one after, as with a pivot of
@@ -198,16 +382,45 @@ __device__ __forceinline__ int tri_sturm_f(const float2* de, float x) {
   return cnt;
 }
 
-// Stage 2: tw.lamf = eigenvalues of T, descending.
-template <int D, typename T, int NT>
-__device__ void tri_eigvals(TriWork<D, T, NT>& tw) {
-  constexpr int G = NT / D;
-  static_assert(G >= 2 && G <= 64 && (G & (G - 1)) == 0, "group of lanes per eigenvalue");
-  constexpr int ROUNDS = G >= 16 ? 7 : (G >= 8 ? 9 : 16);
+// Multisection by groups of G lanes: tw.lamf[t], t < need, = the t-th largest
+// eigenvalue, from the interval [glo, ghi]; each round divides a bracket by
+// G + 1, and the rounds take it below float resolution.
+template <int G, int D, typename T, int NT>
+__device__ void tri_multisect(TriWork<D, T, NT>& tw, int need) {
+  constexpr int ROUNDS = G >= 16 ? 7 : 9;
   const int tid = threadIdx.x;
+  const int t = tid / G, sl = tid % G;  // eigenvalue, lane of its group
+  if (t >= need) return;  // whole groups
+  const int j = D - 1 - t;              // its ascending index
+  float a = tw.glo, b = tw.ghi;
+  for (int rnd = 0; rnd < ROUNDS; ++rnd) {
+    const float h = (b - a) / (float)(G + 1);
+    const float x = fmaf((float)(sl + 1), h, a);
+    const int below = tri_sturm_f<D>(tw.de, x) <= j;  // lambda_j >= x
+    // the points whose count is <= j form a prefix of the group
+    int u = 0;
+#pragma unroll
+    for (int o = 0; o < G; ++o) u += __shfl(below, (tid & ~(G - 1)) + o);
+    const float na = u == 0 ? a : fmaf((float)u, h, a);
+    const float nb = u == G ? b : fmaf((float)(u + 1), h, a);
+    a = na;
+    b = fmaxf(nb, na);
+  }
+  if (sl == 0) tw.lamf[t] = 0.5f * (a + b);
+}
+
+// Stage 2: tw.lamf[t], t < min(need, D) = the leading eigenvalues of T,
+// descending.  The rounds are bound by instruction issue once every SIMD has
+// more than two waves, so few eigenvalues take 16 lanes each (seven rounds)
+// and many take 8 (nine rounds).
+template <int D, typename T, int NT>
+__device__ void tri_eigvals(TriWork<D, T, NT>& tw, int need) {
+  static_assert(NT >= 8 * D, "8 lanes per eigenvalue");
+  const int tid = threadIdx.x;
+  need = min(need, D);
   if (tid < D) {
-    tw.e2[tid] = tw.e[tid] * tw.e[tid];
     tw.de[tid] = make_float2((float)tw.d[tid], tid > 0 ? fmaxf((float)(tw.e[tid - 1] * tw.e[tid - 1]), FLT_MIN) : 0.f);
+    tw.lamf[tid] = 0.f;
   }
   __syncthreads();
   if (tid < 64) {
@@ -218,7 +431,7 @@ __device__ void tri_eigvals(TriWork<D, T, NT>& tw) {
       const float r = (float)(fabs(tw.e[i]) + (i > 0 ? fabs(tw.e[i - 1]) : 0.0));
       lo = fminf(lo, (float)tw.d[i] - r);
       hi = fmaxf(hi, (float)tw.d[i] + r);
-      md2 = fmax(md2, tw.e2[i]);
+      md2 = fmax(md2, tw.e[i] * tw.e[i]);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
@@ -235,23 +448,20 @@ __device__ void tri_eigvals(TriWork<D, T, NT>& tw) {
     }
   }
   __syncthreads();
-  const int j = tid / G, sl = tid % G;  // ascending index j, lane sl of its group
-  float a = tw.glo, b = tw.ghi;
-  for (int rnd = 0; rnd < ROUNDS; ++rnd) {
-    const float h = (b - a) / (float)(G + 1);
-    const float x = fmaf((float)(sl + 1), h, a);
-    const int below = tri_sturm_f<D>(tw.de, x) <= j;  // lambda_j >= x
-    // the points whose count is <= j form a prefix of the group
-    int u = 0;
-#pragma unroll
-    for (int o = 0; o < G; ++o) u += __shfl(below, (tid & ~(G - 1)) + o);
-    const float na = u == 0 ? a : fmaf((float)u, h, a);
-    const float nb = u == G ? b : fmaf((float)(u + 1), h, a);
-    a = na;
-    b = fmaxf(nb, na);
-  }
-  if (sl == 0) tw.lamf[D - 1 - j] = 0.5f * (a + b);
+  if (need * 16 <= NT / 2)
+    tri_multisect<16, D, T, NT>(tw, need);
+  else
+    tri_multisect<8, D, T, NT>(tw, need);
   __syncthreads();
+}
+
+// Reciprocal to about 1 ulp: the hardware estimate and two Newton steps, a
+// third of an IEEE division's dependent chain.  Pivots stay within
+// [DBL_MIN, 1 / DBL_MIN] in magnitude (tri_guard and the floor's scale).
+__device__ __forceinline__ double tri_rcp(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
 }
 
 template <int D>
@@ -261,33 +471,33 @@ __device__ __forceinline__ double tri_guard(double x, double piv) {
 
 // One chain of the twisted factorisation of T - lam I for vector t: the
 // stationary pivots dp (top down, `fwd`) or the progressive pivots dm
-// (bottom up), each with the ratios that build the vector,
-// rho_i = e_i / dp_i and sig_i = e_i / dm_{i+1}.  scr holds [4][D][D]
-// doubles (dp, dm, rho, sig), entry (i, t) at i * D + t, so that each
-// wave's accesses are contiguous.
-template <int D, typename T, int NT>
-__device__ void tri_chain(const TriWork<D, T, NT>& tw, double lam, double* __restrict__ scr, int t,
-                          bool fwd) {
+// (bottom up).  scr holds [2][D][D] doubles (dp, dm), entry (i, t) at
+// i * D + t, so that each wave's accesses are contiguous.  SEQ divides and
+// keeps the ratios rho_i = e_i / dp_i and sig_i = e_i / dm_{i+1} in rat
+// ([2][D][D], the same layout).
+template <int D, bool SEQ, typename T, int NT>
+__device__ void tri_chain(const TriWork<D, T, NT>& tw, double lam, double* __restrict__ scr,
+                          double* __restrict__ rat, int t, bool fwd) {
   const double piv = tw.pivd;
   if (fwd) {
     double* __restrict__ sdp = scr;
-    double* __restrict__ srho = scr + 2 * D * D;
     double dp = tri_guard<D>(tw.d[0] - lam, piv);
     sdp[t] = dp;
+#pragma unroll 8
     for (int i = 0; i < D - 1; ++i) {
-      const double rho = tw.e[i] / dp;
-      srho[i * D + t] = rho;
+      const double rho = SEQ ? tw.e[i] / dp : tw.e[i] * tri_rcp(dp);
+      if (SEQ) rat[i * D + t] = rho;
       dp = tri_guard<D>((tw.d[i + 1] - lam) - tw.e[i] * rho, piv);
       sdp[(i + 1) * D + t] = dp;
     }
   } else {
     double* __restrict__ sdm = scr + D * D;
-    double* __restrict__ ssig = scr + 3 * D * D;
     double dm = tri_guard<D>(tw.d[D - 1] - lam, piv);
     sdm[(D - 1) * D + t] = dm;
+#pragma unroll 8
     for (int i = D - 2; i >= 0; --i) {
-      const double sig = tw.e[i] / dm;
-      ssig[i * D + t] = sig;
+      const double sig = SEQ ? tw.e[i] / dm : tw.e[i] * tri_rcp(dm);
+      if (SEQ) rat[D * D + i * D + t] = sig;
       dm = tri_guard<D>((tw.d[i] - lam) - tw.e[i] * sig, piv);
       sdm[i * D + t] = dm;
     }
@@ -301,10 +511,10 @@ __device__ void tri_chain(const TriWork<D, T, NT>& tw, double lam, double* __res
 // to row when `store`; returns the sum of the squares of the unscaled
 // entries.  Ratios are loaded 16 at a time ahead of the dependent products.
 template <int D, typename T>
-__device__ double tri_sweep(const double* __restrict__ scr, int t, int r, bool up, double scale, bool store,
+__device__ double tri_sweep(const double* __restrict__ rat, int t, int r, bool up, double scale, bool store,
                             T* __restrict__ row) {
   // step j uses ratio index up ? r-1-j : r+j and stores entry r -/+ (1+j)
-  const double* __restrict__ base = up ? scr + 2 * D * D : scr + 3 * D * D;
+  const double* __restrict__ base = up ? rat : rat + D * D;
   const int len = up ? r : D - 1 - r;
   const int dir = up ? -1 : 1;
   const int i0 = up ? r - 1 : r;
@@ -325,29 +535,102 @@ __device__ double tri_sweep(const double* __restrict__ scr, int t, int r, bool u
   return nrm;
 }
 
-// Stage 3.  VT: row t (stride LV) receives the eigenvector of lamf[t] for
-// t < nvec (tridiagonal coordinates); tw.lamv[t] its corrected eigenvalue.
-// scr: this block's [4][D][D] doubles of global scratch.  The two pivot
-// chains of a factorisation run in different waves; the twist search, the
-// product sweeps and the checks use a group of 8 lanes per vector.
+// Entries of the twisted vector (z_r = 1), D / 8 consecutive ones per lane of
+// the vector's group of 8 (lane s): above r, z_i = f_i z_{i+1} with
+// f_i = -e_i / dp_i; below it, z_i = f_i z_{i-1} with f_i = -e_{i-1} / dm_i.
+// Each lane forms its ratios and their running products from its end nearer
+// r, then multiplies them by the products of the lanes between.  Returns the
+// group's sum of squares.
 template <int D, typename T, int NT>
-__device__ void tri_vectors(TriWork<D, T, NT>& tw, T* VT, int LV, int nvec, double* scr) {
-  static_assert(NT >= 8 * D && D % 8 == 0, "8 lanes per vector");
+__device__ double tri_twisted(const TriWork<D, T, NT>& tw, const double* __restrict__ scr, int t, int r,
+                              int s, double* z) {
+  constexpr int NE = D / 8;
+  const int i0 = s * NE;
+#pragma unroll
+  for (int u = 0; u < NE; ++u) {
+    const int i = i0 + u;
+    z[u] = scr[(i < r ? 0 : D * D) + i * D + t];
+  }
+#pragma unroll
+  for (int u = 0; u < NE; ++u) {
+    const int i = i0 + u;
+    const double e = tw.e[i < r ? i : (i > r ? i - 1 : 0)];
+    z[u] = i == r ? 1.0 : -e * tri_rcp(z[u]);
+  }
+  // products within the lane: downwards for the entries after r, upwards for
+  // those before it (entry r is 1 in both)
+#pragma unroll
+  for (int u = 1; u < NE; ++u)
+    if (i0 + u > r) z[u] *= i0 + u - 1 >= r ? z[u - 1] : 1.0;
+#pragma unroll
+  for (int u = NE - 2; u >= 0; --u)
+    if (i0 + u < r) z[u] *= i0 + u + 1 <= r ? z[u + 1] : 1.0;
+  // the whole lane's product towards the far side: its last entry (below r)
+  // or its first (above r); lanes are combined in order of distance from r
+  const int sr = r / NE, lane0 = (threadIdx.x & 63) & ~7;
+  const double far = s >= sr ? z[NE - 1] : z[0];
+  double m = 1.0;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    // lane sr itself is cut at r: its two sides' products are its end entries
+    const double lo = __shfl(far, lane0 + j), first = __shfl(z[0], lane0 + j);
+    if (s > sr && j >= sr && j < s) m *= lo;
+    if (s < sr && j <= sr && j > s) m *= j == sr ? first : lo;
+  }
+  double nrm = 0.0;
+#pragma unroll
+  for (int u = 0; u < NE; ++u) {
+    if (s != sr) z[u] *= m;
+    nrm += z[u] * z[u];
+  }
+  return tri_group_sum<8>(nrm);
+}
+
+// Stage 3.  VT: row t (stride LV) receives the eigenvector of lamf[t] for
+// t < nvec (tridiagonal coordinates); tw.lamv[t] its corrected eigenvalue
+// (lamf[nvec], when nvec < D, is read for the gap below the last one).
+// scr, rat: this block's [2][D][D] doubles of global scratch each (rat for
+// SEQ only).  The two pivot
+// chains of a factorisation run in different waves; the twist search, the
+// vector's products and the checks use a group of 8 lanes per vector.
+// SEQ: IEEE divisions, the products one after another in two lanes, and
+// exactly one correction.
+template <int D, bool SEQ, typename T, int NT>
+__device__ void tri_vectors(TriWork<D, T, NT>& tw, T* VT, int LV, int nvec, double* scr, double* rat) {
+  static_assert(NT >= 8 * D && D % 32 == 0, "8 lanes per vector");
+  constexpr int MAXP = 6;
   const int tid = threadIdx.x;
   const int t8 = tid >> 3, s8 = tid & 7;  // vector and lane of its group
   if (tid < D) tw.lamv[tid] = (double)tw.lamf[tid];
-  if (tid == 0) tw.ok = 1;
+  if (tid == 0) {
+    tw.ok = 1;
+    tw.again = 0;
+  }
   __syncthreads();
-  for (int pass = 0; pass < 2; ++pass) {
+  const double tn = fmax((double)tw.fnorm, DBL_MIN);
+  // a correction of size c leaves the vector about c / gap of its neighbours
+  double conv = 0.0;
+  if (t8 < nvec) {
+    double gap = tn;
+    if (t8 > 0) gap = fmin(gap, (double)tw.lamf[t8 - 1] - (double)tw.lamf[t8]);
+    if (t8 + 1 < D) gap = fmin(gap, (double)tw.lamf[t8] - (double)tw.lamf[t8 + 1]);
+    conv = sizeof(T) == 4 ? fmax(1e-7 * gap, 1e-14 * tn) : fmax(1e-12 * gap, 4e-15 * tn);
+  }
+  T* row = VT + (size_t)t8 * LV;
+  constexpr int NE = D / 8;
+  for (int pass = 0;; ++pass) {
     // pivot chains: threads [0, D) bottom up, [D, 2D) top down
-    if (tid < 2 * D && (tid % D) < nvec) tri_chain<D, T, NT>(tw, tw.lamv[tid % D], scr, tid % D, tid >= D);
+    if (tid < 2 * D && (tid % D) < nvec) tri_chain<D, SEQ>(tw, tw.lamv[tid % D], scr, rat, tid % D, tid >= D);
     __syncthreads();
+    double nrm = 1.0, corr = 0.0, z[SEQ ? 1 : NE];
+    int r = 0;
     if (t8 < nvec) {
       const int t = t8;
       const double lam = tw.lamv[t];
       // twist index: smallest |gamma_k|, k = s8 + 8j; ties to the smaller k
       double bg = 0.0, ba = -1.0;
       int bk = D;
+#pragma unroll 8
       for (int k = s8; k < D; k += 8) {
         const double gk = scr[k * D + t] + scr[D * D + k * D + t] - (tw.d[k] - lam);
         const double ak = fabs(gk);
@@ -368,50 +651,71 @@ __device__ void tri_vectors(TriWork<D, T, NT>& tw, T* VT, int LV, int nvec, doub
       take(tri_dpp<kDppXor2>(ba), tri_dpp<kDppXor2>(bg), __builtin_amdgcn_mov_dpp(bk, kDppXor2, 0xF, 0xF, true));
       take(tri_dpp<kDppHalfMirror>(ba), tri_dpp<kDppHalfMirror>(bg),
            __builtin_amdgcn_mov_dpp(bk, kDppHalfMirror, 0xF, 0xF, true));
-      const int r = bk;
-      // |z|^2 from the two sides (lanes 0 and 1 of the group)
-      T* row = VT + (size_t)t * LV;
-      double side = s8 < 2 ? tri_sweep<D, T>(scr, t, r, s8 == 0, 1.0, false, row) : 0.0;
-      side += tri_dpp<kDppXor1>(side);
-      const double nrm = 1.0 + side;
-      if (pass == 0) {
-        if (s8 == 0) tw.lamv[t] = lam + bg / nrm;
-      } else if (s8 < 2) {
-        const double sc = 1.0 / sqrt(nrm);
-        if (s8 == 0) row[r] = (T)sc;
-        tri_sweep<D, T>(scr, t, r, s8 == 0, sc, true, row);
+      // one lane's choice for the group (NaN pivots can leave them apart)
+      r = __shfl(bk, (tid & 63) & ~7);
+      if constexpr (SEQ) {
+        // the first pass needs |z|^2 for the correction, the last one to
+        // normalise
+        double side = s8 < 2 ? tri_sweep<D, T>(rat, t, r, s8 == 0, 1.0, false, row) : 0.0;
+        side += tri_dpp<kDppXor1>(side);
+        nrm = 1.0 + side;
+      } else {
+        nrm = tri_twisted<D, T, NT>(tw, scr, t, r, s8, z);
       }
+      corr = bg / nrm;
+      const bool next = SEQ ? pass == 0 : pass + 1 < MAXP && !(fabs(corr) <= conv);
+      if (s8 == 0 && next) tw.again = 1;
     }
     __syncthreads();
+    const bool more = tw.again;
+    if (t8 < nvec) {
+      if (!more) {
+        const double sc = 1.0 / sqrt(nrm);
+        if constexpr (SEQ) {
+          if (s8 == 0) row[r] = (T)sc;
+          if (s8 < 2) tri_sweep<D, T>(rat, t8, r, s8 == 0, sc, true, row);
+        } else {
+#pragma unroll
+          for (int u = 0; u < NE; ++u) row[s8 * NE + u] = (T)(z[u] * sc);
+        }
+      }
+      if (s8 == 0 && (!SEQ || more)) tw.lamv[t8] += corr;
+    }
+    __syncthreads();
+    if (!more) break;
+    if (tid == 0) tw.again = 0;
   }
-  // residual |T z - lam z| per vector (8 lanes), then pairwise orthogonality
-  const double tol = sizeof(T) == 4 ? 1e-4 : 1e-9;
-  const double tn = fmax((double)tw.fnorm, DBL_MIN);
+  // residual |T z - lam z| per vector (8 lanes), then pairwise orthogonality:
+  // each group keeps its vector in registers and meets the later ones
+  constexpr int NC = D / 32;  // 4-entry pieces per lane: piece j starts at (8 j + s8) * 4
+  typedef T T4 __attribute__((ext_vector_type(4)));
+  const T tol = sizeof(T) == 4 ? T(1e-4) : T(1e-9);
   bool bad = false;
   if (t8 < nvec) {
-    const T* z = VT + (size_t)t8 * LV;
     const double lam = tw.lamv[t8];
     double res = 0.0;
     for (int i = s8; i < D; i += 8) {
-      double y = (tw.d[i] - lam) * (double)z[i];
-      if (i > 0) y += tw.e[i - 1] * (double)z[i - 1];
-      if (i < D - 1) y += tw.e[i] * (double)z[i + 1];
+      double y = (tw.d[i] - lam) * (double)row[i];
+      if (i > 0) y += tw.e[i - 1] * (double)row[i - 1];
+      if (i < D - 1) y += tw.e[i] * (double)row[i + 1];
       res = fmax(res, fabs(y));
     }
-    bad = !(res <= tol * tn);
-  }
-  const int npair = nvec * (nvec - 1) / 2;
-  for (int pi = tid; pi < npair; pi += NT) {
-    // pair index -> (a, b), a < b
-    int a = (int)((sqrt(8.0 * pi + 1.0) - 1.0) * 0.5);
-    while ((a + 1) * (a + 2) / 2 <= pi) ++a;
-    while (a * (a + 1) / 2 > pi) --a;
-    const int bb = a + 1, aa = pi - a * (a + 1) / 2;  // bb > aa
-    const T* za = VT + (size_t)aa * LV;
-    const T* zb = VT + (size_t)bb * LV;
-    double dot = 0.0;
-    for (int i = 0; i < D; ++i) dot += (double)za[i] * (double)zb[i];
-    if (!(fabs(dot) <= tol)) bad = true;
+    bad = !(res <= (double)tol * tn);
+    T4 z[NC];
+#pragma unroll
+    for (int j = 0; j < NC; ++j) z[j] = *(const T4*)(row + (8 * j + s8) * 4);
+    // from the first vector after the wave's first: uniform over the wave
+    for (int b = __builtin_amdgcn_readfirstlane(t8) + 1; b < nvec; ++b) {
+      const T* zb = VT + (size_t)b * LV;
+      T dot = 0;
+#pragma unroll
+      for (int j = 0; j < NC; ++j) {
+        const T4 y = *(const T4*)(zb + (8 * j + s8) * 4);
+        dot += (z[j].x * y.x + z[j].y * y.y) + (z[j].z * y.z + z[j].w * y.w);
+      }
+      dot = tri_group_sum<8>(dot);
+      if (b > t8 && !(fabs(dot) <= tol)) bad = true;
+    }
   }
   if (bad) tw.ok = 0;
   __syncthreads();
@@ -450,6 +754,39 @@ __device__ void tri_back(const T* A, const TriWork<D, T, NT>& tw, T* VT, int LV,
     }
 #pragma unroll
     for (int u = 0; u < NZ; ++u) row[s + GV * u] = z[u];
+  }
+  __syncthreads();
+}
+
+// Stage 4 with the reflectors in the rows of V (tri_reduce_reg).  Vector t belongs to the 8 lanes of one group, each
+// holding D / 8 of its entries in registers for all D - 2 reflectors, in
+// pieces of four so that a reflector is read by 16-byte accesses; group sums
+// go by DPP, so the stage needs no barrier.
+template <int D, typename T, int NT>
+__device__ void tri_back_rows(const T* V, const TriWork<D, T, NT>& tw, T* VT, int LV, int nvec) {
+  constexpr int NC = D / 32;
+  typedef T T4 __attribute__((ext_vector_type(4)));
+  const int tid = threadIdx.x, t = tid >> 3, s = tid & 7;
+  if (t < nvec) {  // whole groups of lanes
+    T* row = VT + (size_t)t * LV;
+    T4 z[NC];
+#pragma unroll
+    for (int j = 0; j < NC; ++j) z[j] = *(const T4*)(row + (8 * j + s) * 4);
+    for (int k = D - 3; k >= 0; --k) {
+      const T b = tw.beta[k];
+      T4 v[NC];
+      T dot = 0;
+#pragma unroll
+      for (int j = 0; j < NC; ++j) {
+        v[j] = *(const T4*)(V + k * D + (8 * j + s) * 4);
+        dot += (v[j].x * z[j].x + v[j].y * z[j].y) + (v[j].z * z[j].z + v[j].w * z[j].w);
+      }
+      const T f = b * tri_group_sum<8>(dot);
+#pragma unroll
+      for (int j = 0; j < NC; ++j) z[j] -= f * v[j];
+    }
+#pragma unroll
+    for (int j = 0; j < NC; ++j) *(T4*)(row + (8 * j + s) * 4) = z[j];
   }
   __syncthreads();
 }

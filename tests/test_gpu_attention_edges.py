@@ -53,3 +53,40 @@ def test_probe_rows_and_output_over_short_splits(orc, dtype, grid, m):
         assert rel_l2(ex["o_dense_probes"], ref) < tol
         out, _ = _replay(orc, r, ex, 0, h)
         assert rel_l2(r["out"][0, h], out) < tol
+
+
+# the eigensolver's own convergence: a basis of every dimension (d = 64 keeps
+# r_Q = d directions, down to the noise floor's close eigenvalues) comes from
+# the tridiagonal solver, in both precisions, and the fit from few and many
+# directions (1, one past a lane group's 16, d).  Ranks that reach eigenvalues
+# below 1e-5 of the largest are left to Jacobi in double by design.
+@pytest.mark.parametrize("dtype,d,rank", [("f32", 64, 1), ("bf16", 64, 17), ("f32", 128, 17),
+                                          ("bf16", 128, 1), ("f32", 128, 100), ("bf16", 128, 100),
+                                          ("f32", 64, 64)])
+def test_eigensolver_without_jacobi_and_fit_ranks(orc, dtype, d, rank):
+    from paper_2608_18484_amd import sparsepr as S
+    wl = medium(grid=(3, 16, 24), heads=2, dtype=dtype, d=d, n_probes=140, resid_rank=rank)
+    r = _run(wl)
+    if rank <= 17:
+        assert not r["op"].stats()["status_flags"] & S.FLAG_EIG_JACOBI
+    for h in range(2):
+        ex = r["op"].export(h, fields=["labels_q", "labels_kv", "routes", "probes", "probe_weights",
+                                       "fit_bpsi", "fit_psi"])
+        out, fit = _replay(orc, r, ex, 0, h)
+        g = ex["fit_bpsi"].astype(np.float64) @ ex["fit_psi"].T.astype(np.float64)
+        assert rel_l2(r["out"][0, h], out) < (1e-5 if dtype == "f32" else 2e-2)
+        if dtype == "f32":
+            assert rel_l2(g, fit["g"]) < 1e-4
+
+
+# a ridge matrix that is not positive definite (no ridge, fewer probes than
+# dimensions): the flag is raised and the correction is the mean residual
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 128)])
+def test_fit_not_positive_definite(dtype, d):
+    from paper_2608_18484_amd import sparsepr as S
+    wl = medium(grid=(2, 16, 24), heads=1, dtype=dtype, d=d, n_probes=9, resid_rank=4, ridge=0.0)
+    r = _run(wl)
+    ex = r["op"].export(0)
+    if r["op"].stats()["status_flags"] & S.FLAG_FIT_NOT_PD:
+        assert np.all(ex["fit_bpsi"] == 0.0)
+    assert np.isfinite(r["out"]).all() or not r["op"].stats()["status_flags"] & S.FLAG_FIT_NOT_PD
