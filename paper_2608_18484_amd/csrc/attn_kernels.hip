@@ -29,7 +29,7 @@
 
 namespace sparsepr {
 
-enum { MODE_SPARSE = 0, MODE_PROBE = 1, MODE_DENSE = 2 };
+enum { MODE_SPARSE = 0, MODE_PROBE = 1, MODE_DENSE = 2 };  // MODE_DENSE: k_attn_f32 only
 
 struct AttnArgs {
   const void* q;
@@ -194,7 +194,7 @@ __device__ __forceinline__ float pair_sum(float x) {
 //  * 128 threads = 2 waves; a block owns up to 64 query rows (32 per wave)
 //    that share one key list: the routed ranges of their query group in the
 //    group-major K/V copy (MODE_SPARSE), or a contiguous slice of the original
-//    K/V rows (MODE_PROBE, MODE_DENSE).
+//    K/V rows (MODE_PROBE).
 //  * 32-key tiles in LDS filled by direct global->LDS 16-byte loads: one K
 //    buffer, refilled with the next tile once every wave has read its score
 //    operands, and two V buffers, the next tile's V loading while the current
@@ -263,8 +263,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     Vp = (const uint16_t*)A.v + base;
   }
   const int64_t ksn = (MODE == MODE_SPARSE) ? D : g.sn;  // row stride of Kp/Vp
-  const int64_t qbase = q_base(g, bh, g.gq);  // also the output's, in MODE_DENSE
-  const uint16_t* Qp = (const uint16_t*)A.q + qbase;
+  const uint16_t* Qp = (const uint16_t*)A.q + q_base(g, bh, g.gq);
 
   // query row of this lane and its B operands
   const int qr = wv * 32 + n;
@@ -540,7 +539,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     }
   } else {
     const float inv = 1.f / l_tot;
-    if (MODE == MODE_SPARSE && !A.seg_last) {
+    if (!A.seg_last) {
       // hand the running state to the next key segment
       float* dst = A.osp + ((size_t)bh * g.N + qrow) * D;
 #pragma unroll
@@ -554,7 +553,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
       float* ml = A.mlst + ((size_t)bh * g.N + qrow) * 4;
       if (h == 0) ml[0] = m_run;
       ml[1 + h] = l_run;
-    } else if (MODE == MODE_SPARSE) {
+    } else {
       float* dst = A.osp + ((size_t)bh * g.N + qrow) * D;
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
@@ -564,21 +563,212 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
           *(float4*)(dst + dv) = make_float4(O[db][i4 * 4] * inv, O[db][i4 * 4 + 1] * inv,
                                              O[db][i4 * 4 + 2] * inv, O[db][i4 * 4 + 3] * inv);
         }
+    }
+  }
+}
+
+// Dense flash attention, bf16 MFMA, fp32 accumulation: the tiles, swizzle and
+// transposed products of k_attn_mfma for contiguous keys.  NW waves of 32 query
+// rows share each 32-key tile, so the copies per row shrink with NW and their
+// addresses are a uniform base plus per-lane constants.  The scores of tile
+// t + 1 are formed next to the exponentials of tile t (an MFMA leaves the issue
+// slots of about six VALU instructions), K and V are double-buffered and the
+// copies of K(t + 2) and V(t + 1) go out at the start of step t, with one
+// barrier per step.
+// 24 heads of 17,160 rows at d = 128: 4.12 -> 3.52 ms (1.03 PFLOP/s); 12 of
+// 4,335 at d = 64: 107 -> 92 us; 2 of 1,275 at d = 128: 35 -> 30 us.  What is
+// left is the matrix pipes' sustained rate on such data: without any copies
+// 3.04 ms, without copies, LDS reads and exponentials 2.9 ms, which is 1.25
+// PFLOP/s; rings of three buffers changed nothing.
+template <int D, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_dense(Geom g, AttnArgs A) {
+  constexpr int KT = 32, CH = D / 8, NKS = D / 16, NDB = D / 32;
+  constexpr int NCP = KT * CH / 64, CPW = NCP / NW;  // 1 KB copies per tensor and tile, per wave
+  constexpr uint32_t TB = KT * D * 2;                // bytes of a tile
+  static_assert(NCP % NW == 0, "copies divide among the waves");
+  __shared__ __attribute__((aligned(1024))) uint16_t kt[2][KT * D], vt[2][KT * D];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 31, h = lane >> 5;
+  // Block order: with a multiple of 8 query heads, XCD x takes heads x, x + 8,
+  // ... so that its L2 holds one head's keys; otherwise blocks go head by head.
+  const int tiles = (g.N + 32 * NW - 1) / (32 * NW), heads = g.BH * g.G;
+  int bq, tile;
+  if (heads % 8 == 0) {
+    const int b = blockIdx.x >> 3;
+    bq = (b / tiles) * 8 + (blockIdx.x & 7);
+    tile = b % tiles;
+  } else {
+    bq = blockIdx.x / tiles;
+    tile = blockIdx.x % tiles;
+  }
+  // query heads of one K/V head follow each other
+  const int bh = bq / g.G, jq = bq % g.G;
+  const int64_t base = kv_base(g, bh), qbase = q_base(g, bh, jq);
+  const unsigned char* Kp = (const unsigned char*)((const uint16_t*)A.k + base);
+  const unsigned char* Vp = (const unsigned char*)((const uint16_t*)A.v + base);
+  const uint16_t* Qp = (const uint16_t*)A.q + qbase;
+  const int qrow = tile * 32 * NW + wv * 32 + n;
+  const bool qvalid = qrow < g.N;
+  const bool wave_active = tile * 32 * NW + wv * 32 < g.N;
+  bf16x8 qreg[NKS];
+#pragma unroll
+  for (int ks = 0; ks < NKS; ++ks) {
+    uint4 u = make_uint4(0, 0, 0, 0);
+    if (qvalid) u = *(const uint4*)(Qp + (int64_t)qrow * g.sn + ks * 16 + h * 8);
+    qreg[ks] = __builtin_bit_cast(bf16x8, u);
+  }
+  constexpr int kWaitLgkm0 = 0xC07F, kWaitVm0 = 0x3f70;
+  __builtin_amdgcn_s_waitcnt(kWaitVm0);
+
+  const int ntile = (g.N + KT - 1) / KT;
+  const uint32_t row_bytes = (uint32_t)(g.sn * 2);
+  auto lds_of = [](const void* p) {
+    return __builtin_amdgcn_readfirstlane(
+        (uint32_t)(size_t)(const __attribute__((address_space(3))) void*)p);
+  };
+  const uint32_t kdst = lds_of(&kt[0][0]), vdst = lds_of(&vt[0][0]);
+  // this lane's key and 16-byte chunk of the wave's copies
+  int ckey[CPW];
+  uint32_t cchunk[CPW], voff[CPW];
+#pragma unroll
+  for (int u = 0; u < CPW; ++u) {
+    const int s = (u * NW + wv) * 64 + lane;
+    ckey[u] = s / CH;
+    cchunk[u] = (uint32_t)(((s % CH) ^ kv_swz<D>(ckey[u])) * 16);
+    voff[u] = (uint32_t)ckey[u] * row_bytes + cchunk[u];
+  }
+  auto issue = [&](int t, const unsigned char* src, uint32_t dst) {
+    const unsigned char* p = src + (size_t)t * KT * row_bytes;
+    const int left = g.N - t * KT;  // keys past the end repeat the last one
+    if (left >= KT) {
+#pragma unroll
+      for (int u = 0; u < CPW; ++u) g2lds16s(p, voff[u], dst + (uint32_t)((u * NW + wv) * 1024));
     } else {
-      uint16_t* dst = (uint16_t*)A.out + qbase + (int64_t)qrow * g.sn;
+#pragma unroll
+      for (int u = 0; u < CPW; ++u)
+        g2lds16s(p, (uint32_t)min(ckey[u], left - 1) * row_bytes + cchunk[u],
+                 dst + (uint32_t)((u * NW + wv) * 1024));
+    }
+  };
+  const float sl2 = 1.4426950408889634f / sqrtf((float)D);
+  float m_run = -INFINITY, l_run = 0.f, mt = 0.f;
+  f32x16 O[NDB];
+#pragma unroll
+  for (int db = 0; db < NDB; ++db)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) O[db][i] = 0.f;
+  auto scores = [&](f32x16& S, int b) {
+    bf16x8 kf[NKS];
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks)
+      kf[ks] = __builtin_bit_cast(bf16x8, *(const uint4*)(kt[b] + (n * CH + ((2 * ks + h) ^ kv_swz<D>(n))) * 8));
+#pragma unroll
+    for (int i = 0; i < 16; ++i) S[i] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < NKS; ++ks)
+      S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qreg[ks], S, 0, 0, 0);
+  };
+  // maximum of this lane's scores of tile t, keys past the end masked
+  auto tile_max = [&](f32x16& S, int t) {
+    const int left = g.N - t * KT;
+    if (left < KT) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if ((i >> 2) * 8 + h * 4 + (i & 3) >= left) S[i] = -INFINITY;
+    }
+    mt = fmaxf(fmaxf(S[0], S[1]), S[2]);
+#pragma unroll
+    for (int i = 3; i < 15; i += 2) mt = fmaxf(fmaxf(mt, S[i]), S[i + 1]);
+    mt = fmaxf(mt, S[15]);
+  };
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const bf16x2 one2 = {(__bf16)1.0f, (__bf16)1.0f};
+  // step t: softmax and PV of tile t (scores Sc, buffer b), scores Sn of
+  // tile t + 1 (past the last tile on whatever the buffer holds, unused)
+  auto step = [&](int t, int b, f32x16& Sc, f32x16& Sn) {
+    __builtin_amdgcn_s_waitcnt(kWaitVm0);  // this wave's copies of K(t + 1), V(t)
+    __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+    __builtin_amdgcn_s_barrier();
+    // every wave is done with K(t) and V(t - 1)
+    if (t + 2 < ntile) issue(t + 2, Kp, kdst + (uint32_t)b * TB);
+    if (t + 1 < ntile) issue(t + 1, Vp, vdst + (uint32_t)(1 - b) * TB);
+    if (!wave_active) return;
+    const float mp = pair_max(mt) * sl2;
+    const bool need = mp > m_run + 8.f;
+    if (__ballot(need)) {
+      const float m_new = need ? mp : m_run;
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+      m_run = m_new;
+      l_run *= alpha;
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
 #pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4) {
-          const int dv = db * 32 + i4 * 8 + h * 4;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const __bf16 bv = (__bf16)(O[db][i4 * 4 + e] * inv);
-            dst[dv + e] = __builtin_bit_cast(uint16_t, bv);
-          }
-        }
+        for (int i = 0; i < 16; ++i) O[db][i] *= alpha;
     }
+    scores(Sn, 1 - b);
+    // probabilities rounded to bf16 for the PV product; the row sum is taken
+    // over the same rounded values (two per dot2), so O and l share one set
+    // of weights
+    bf16x8 P[2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        P[c][e] = (__bf16)__builtin_amdgcn_exp2f(fmaf(Sc[c * 8 + e], sl2, -m_run));
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int e = 0; e < 8; e += 2) {
+        const bf16x2 pp = {P[c][e], P[c][e + 1]};
+        l_run = __builtin_amdgcn_fdot2_f32_bf16(pp, one2, l_run, false);
+      }
+    const int grp = lane >> 4, gl = lane & 15;
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int db = 0; db < NDB; ++db) {
+        const int dv = db * 32 + 16 * (grp & 1) + 4 * (gl & 3);
+        const int key0 = 16 * c + 4 * h + (gl >> 2);
+        const int key1 = key0 + 8;
+        const v4i16 lo = lds_read_tr16(vt[b] + (key0 * CH + ((dv >> 3) ^ kv_swz<D>(key0))) * 8 + (dv & 7));
+        const v4i16 hi = lds_read_tr16(vt[b] + (key1 * CH + ((dv >> 3) ^ kv_swz<D>(key1))) * 8 + (dv & 7));
+        const bf16x8 vf = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+        O[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, P[c], O[db], 0, 0, 0);
+      }
+    tile_max(Sn, t + 1);
+  };
+  f32x16 S0, S1;
+  issue(0, Kp, kdst);
+  issue(0, Vp, vdst);
+  if (ntile > 1) issue(1, Kp, kdst + TB);
+  __builtin_amdgcn_s_waitcnt(kWaitVm0);
+  __builtin_amdgcn_s_barrier();
+  scores(S0, 0);
+  tile_max(S0, 0);
+  for (int t = 0; t < ntile; t += 2) {
+    step(t, 0, S0, S1);
+    if (t + 1 < ntile) step(t + 1, 1, S1, S0);
   }
+  // every copy has landed before the block can end
+  __builtin_amdgcn_s_waitcnt(kWaitVm0);
+  if (!qvalid) return;
+  const float inv = 1.f / pair_sum(l_run);
+  uint16_t* dst = (uint16_t*)A.out + qbase + (int64_t)qrow * g.sn;
+#pragma unroll
+  for (int db = 0; db < NDB; ++db)
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4) {
+      const int dv = db * 32 + i4 * 8 + h * 4;
+      uint32_t o[2];
+#pragma unroll
+      for (int e = 0; e < 4; e += 2) {
+        const uint16_t lo = __builtin_bit_cast(uint16_t, (__bf16)(O[db][i4 * 4 + e] * inv));
+        const uint16_t hi = __builtin_bit_cast(uint16_t, (__bf16)(O[db][i4 * 4 + e + 1] * inv));
+        o[e >> 1] = (uint32_t)lo | ((uint32_t)hi << 16);
+      }
+      *(uint2*)(dst + dv) = make_uint2(o[0], o[1]);
+    }
 }
 
 // Group-major copies of K and V (Sec. 4.3): position p of head bh holds row
@@ -927,11 +1117,15 @@ static void dense_d(const Geom& g, const AttnArgs& a, hipStream_t s) {
     k_attn_f32<D, MODE_DENSE><<<dim3(tiles, 1, g.BH * g.G), 256, 0, s>>>(g, a);
     return;
   }
-  for (int j = 0; j < g.G; ++j) {  // every query head of each K/V head
-    Geom h = g;
-    h.gq = j;
-    k_attn_mfma<D, MODE_DENSE><<<dim3(tiles, g.BH), 128, 0, s>>>(h, a);
-  }
+  // Four waves share a tile's copies when such blocks fill the chip twice
+  // over (24 heads of 17,160 rows: 3.52 ms, with two waves 3.91); shorter
+  // launches spread over twice the blocks (2 heads of 1,275 rows: 29.7 us,
+  // with four waves 31.2; 12 of 4,335 at d = 64: 92 us either way).
+  const int64_t heads = (int64_t)g.BH * g.G, blocks4 = (g.N + 127) / 128 * heads;
+  if (blocks4 >= 512)
+    k_attn_dense<D, 4><<<(unsigned)blocks4, 256, 0, s>>>(g, a);
+  else
+    k_attn_dense<D, 2><<<(unsigned)((g.N + 63) / 64 * heads), 128, 0, s>>>(g, a);
 }
 
 void launch_dense(const Geom& g, const void* q, const void* k, const void* v, void* out,

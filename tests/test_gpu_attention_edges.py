@@ -37,6 +37,21 @@ def test_dense_attention_edges(n, dtype, d, heads, kv):
     assert rel_l2(got, ref) < (1e-5 if dtype == "f32" else 2e-2)
 
 
+# the block orders of the bf16 kernel (head counts divisible by 8 and not) at
+# both of its block sizes, with a short last tile of rows and of keys
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("batch,heads,kv,n", [(1, 8, 8, 77), (3, 5, 5, 4400), (2, 12, 3, 2800)])
+def test_dense_attention_block_orders(d, batch, heads, kv, n):
+    from paper_2608_18484_amd import sparsepr as S
+    g = torch.Generator().manual_seed(n + d)
+    q, k, v = (torch.randn(batch, h, n, d, generator=g).bfloat16() for h in (heads, kv, kv))
+    got = S.dense_attention(q.cuda(), k.cuda(), v.cuda()).cpu().double()
+    rows = torch.tensor([0, 31, 63, n // 2, n - 1])
+    rep = heads // kv
+    ref = _dense64(q[:, :, rows], k.repeat_interleave(rep, 1), v.repeat_interleave(rep, 1))
+    assert rel_l2(got[:, :, rows], ref) < 2e-2
+
+
 # probe rows over key splits: the last split short, one and two tiles of
 # probes, more splits than the shortest split allows at this length
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
