@@ -410,11 +410,9 @@ __global__ __launch_bounds__(1024) void k_fit_solve(Geom g, Work w) {
 // final_reconstructed_output): out_i = x_i + mu_R + ((x_i - mu_x)/s_x) Y Psi^T
 // for the video rows; dense-prefix rows keep their (exact) sparse output.
 // Probe rows are overwritten afterwards by k_probe_scatter.
-constexpr int CORR_CHUNKS = 8;
-
 template <int D>
-__global__ __launch_bounds__(256) void k_correct(Geom g, Work w, void* out) {
-  // CORR_CHUNKS chunks of 64 rows per block.  Thread (row = tid / 4,
+__global__ __launch_bounds__(256) void k_correct(Geom g, Work w, void* out, int chunks) {
+  // `chunks` chunks of 64 rows per block.  Thread (row = tid / 4,
   // quarter = tid % 4) owns the columns [quarter * D/4, quarter * D/4 + D/4)
   // of its row, held in registers; its partial of t = xbar Y
   // (Y = B_lambda Psi) over those columns is summed with the other quarters'
@@ -447,9 +445,9 @@ __global__ __launch_bounds__(256) void k_correct(Geom g, Work w, void* out) {
   for (int i = tid; i < 3 * D; i += 256) fvs[i / D][i % D] = i / D == 1 ? 1.f / fv[i] : fv[i];
   if (one_slice) stage(0);
   __syncthreads();
-  for (int chunk = 0; chunk < CORR_CHUNKS; ++chunk) {
-    const int row = (blockIdx.x * CORR_CHUNKS + chunk) * 64 + rw;
-    if ((blockIdx.x * CORR_CHUNKS + chunk) * 64 >= g.N) break;  // uniform over the block
+  for (int chunk = 0; chunk < chunks; ++chunk) {
+    const int row = (blockIdx.x * chunks + chunk) * 64 + rw;
+    if ((blockIdx.x * chunks + chunk) * 64 >= g.N) break;  // uniform over the block
     const bool valid = row < g.N;
     const bool text = row < g.ntext;
     const float* src = w.osp + ((size_t)bq * g.N + (valid ? row : 0)) * D + qtr * CW;
@@ -563,7 +561,8 @@ static void fit_d(const Geom& g, const Work& w0, void* out, hipStream_t s, hipEv
   else
     k_fit_solve<D, float><<<BQ, 1024, 0, s>>>(g, w0);
   if (ev) (void)hipEventRecord(ev[3], s);
-  k_correct<D><<<dim3((g.N + 64 * CORR_CHUNKS - 1) / (64 * CORR_CHUNKS), BQ), 256, 0, s>>>(g, w0, out);
+  const int chunks = row_chunks(g.N, BQ);
+  k_correct<D><<<dim3((g.N + 64 * chunks - 1) / (64 * chunks), BQ), 256, 0, s>>>(g, w0, out, chunks);
   if (g.M > 0) k_probe_scatter<<<dim3(g.M, BQ), 128, 0, s>>>(g, w0, out);
   if (ev) (void)hipEventRecord(ev[4], s);
 }

@@ -213,13 +213,12 @@ __global__ __launch_bounds__(1024) void k_eig_basis(const double* gram, int r, f
 // head; G = 1 is the single-head case).
 // ---------------------------------------------------------------------------
 
-constexpr int PROJ_CHUNKS = 8;
 
 template <int D, int MAXR, bool MF>
 __global__ __launch_bounds__(256) void k_project(const void* x, Geom g, const float* F, int R,
                                                  int query, int rms, float eps, float* phi,
                                                  int64_t* stats, uint16_t* xhi, uint16_t* xlo,
-                                                 float* xn, int RP) {
+                                                 float* xn, int RP, int chunks) {
   // MF (bf16 inputs): the products run on MFMA.  F is split into three bf16
   // parts (hi + mid + lo reproduce its float value), each bf16 input times a
   // part is exact in float, so the accumulation is the only rounding, as in
@@ -277,9 +276,9 @@ __global__ __launch_bounds__(256) void k_project(const void* x, Geom g, const fl
   const int ty = tid >> 4, tx = tid & 15;
   const int nsrc = query ? g.G : 1;
   bool bad = false;
-  // PROJ_CHUNKS chunks of 64 rows per block share the staged F
-  for (int chunk = 0; chunk < PROJ_CHUNKS; ++chunk) {
-    const int r0 = (blockIdx.x * PROJ_CHUNKS + chunk) * ROWS;
+  // `chunks` chunks of 64 rows per block share the staged F
+  for (int chunk = 0; chunk < chunks; ++chunk) {
+    const int r0 = (blockIdx.x * chunks + chunk) * ROWS;
     if (r0 >= g.NV) break;
     if (chunk > 0) __syncthreads();
     float pooled[4][CPT];
@@ -1022,13 +1021,46 @@ __global__ __launch_bounds__(1024) void k_sort_scan(KmArgs a, int it) {
   if (tid == 0) off[a.C] = total;
 }
 
+// One slice of up to 64 rows [s, min(s + 64, j1)) of the stable scatter, by one
+// wave: each lane reads its label's next slot; the slice's labels go through
+// LDS (sl), every lane marks the lanes holding its label, its stable rank is
+// the number of them before it, and the lane with the last rank advances the
+// slot.
+__device__ __forceinline__ void sort_slice(const int32_t* lab, int s, int j1, int lane, int* pos, int* sl,
+                                           int32_t* perm, int row0) {
+  const uint32_t below_lo = lane >= 32 ? 0xffffffffu : (1u << lane) - 1u;
+  const uint32_t below_hi = lane <= 32 ? 0u : (1u << (lane - 32)) - 1u;
+  const int j = s + lane;
+  const bool valid = j < j1;
+  const int L = valid ? lab[j] : -1 - lane;  // invalid lanes match nothing
+  const int base = valid ? pos[L] : 0;
+  sl[lane] = L;
+  uint32_t mlo = 0u, mhi = 0u;  // lanes holding this lane's label
+#pragma unroll
+  for (int k4 = 0; k4 < 16; ++k4) {
+    const int4 q = *(const int4*)&sl[4 * k4];
+    const int qv[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int k = 4 * k4 + e;
+      if (k < 32)
+        mlo |= (qv[e] == L ? 1u : 0u) << k;
+      else
+        mhi |= (qv[e] == L ? 1u : 0u) << (k - 32);
+    }
+  }
+  const int rank = __popc(mlo & below_lo) + __popc(mhi & below_hi);
+  const int cnt = __popc(mlo) + __popc(mhi);
+  if (valid) {
+    perm[base + rank] = row0 + j;
+    if (rank == cnt - 1) pos[L] = base + cnt;
+  }
+}
+
 // Counting sort, pass 3: stable scatter.  A block of 4 waves takes the
 // block's rows; wave w owns rows [j0 + 256 w, j0 + 256 (w + 1)).  Each wave
 // counts its labels, the per-label slots of the waves follow by a prefix over
-// the waves, and every wave then walks its rows in order, 64 at a time: each
-// lane reads its label's next slot; the slice's labels go through LDS, every
-// lane marks the lanes holding its label, its stable rank is the number of
-// them before it, and the lane with the last rank advances the slot.
+// the waves, and every wave then walks its rows in order, 64 at a time.
 constexpr int kScatterWaves = 4;
 constexpr int kScatterRows = kSortBlock / kScatterWaves;  // rows per wave
 
@@ -1063,35 +1095,7 @@ __global__ __launch_bounds__(256) void k_sort_scatter(KmArgs a, int it) {
   }
   __syncthreads();
   int32_t* perm = a.perm + (size_t)bh * a.N;
-  const uint32_t below_lo = lane >= 32 ? 0xffffffffu : (1u << lane) - 1u;
-  const uint32_t below_hi = lane <= 32 ? 0u : (1u << (lane - 32)) - 1u;
-  for (int s = j0; s < j1; s += 64) {
-    const int j = s + lane;
-    const bool valid = j < j1;
-    const int L = valid ? lab[j] : -1 - lane;  // invalid lanes match nothing
-    const int base = valid ? pos[L] : 0;
-    sl[lane] = L;
-    uint32_t mlo = 0u, mhi = 0u;  // lanes holding this lane's label
-#pragma unroll
-    for (int k4 = 0; k4 < 16; ++k4) {
-      const int4 q = *(const int4*)&sl[4 * k4];
-      const int qv[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int k = 4 * k4 + e;
-        if (k < 32)
-          mlo |= (qv[e] == L ? 1u : 0u) << k;
-        else
-          mhi |= (qv[e] == L ? 1u : 0u) << (k - 32);
-      }
-    }
-    const int rank = __popc(mlo & below_lo) + __popc(mhi & below_hi);
-    const int cnt = __popc(mlo) + __popc(mhi);
-    if (valid) {
-      perm[base + rank] = a.row0 + j;
-      if (rank == cnt - 1) pos[L] = base + cnt;
-    }
-  }
+  for (int s = j0; s < j1; s += 64) sort_slice(lab, s, j1, lane, pos, sl, perm, a.row0);
 }
 
 // Centroid update: per group, double sums of the members' coordinates in
@@ -1099,17 +1103,14 @@ __global__ __launch_bounds__(256) void k_sort_scatter(KmArgs a, int it) {
 // float; an empty group keeps its centroid (and its assignment operands).
 // One wave per group: the members' rows are fetched 64 at a time (lane i
 // holds member m0 + i) and exchanged by readlane; lane l owns coordinates l
-// and l + 64, whose values are loaded sixteen members at a time and added in
-// ascending member order.
-__global__ __launch_bounds__(256) void k_km_update(KmArgs a, int it) {
-  const int bh = blockIdx.y, wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  if (km_changed(a, bh)[it] == 0) return;
-  const int b = blockIdx.x * 4 + wv;
-  if (b >= a.C) return;
-  const int32_t* off = a.off + (size_t)bh * a.offstride;
-  const int32_t* perm = a.perm + (size_t)bh * a.N;
-  const int s0 = __builtin_amdgcn_readfirstlane(off[b]), s1 = __builtin_amdgcn_readfirstlane(off[b + 1]);
+// and l + 64, added in ascending member order.  All 64 members' loads are in
+// flight together (with 16 in flight a group of 64 rows paid four memory round
+// trips and a large one dozens: 24 us an update at two heads of 1,024 rows).
+// `cw`: 128 floats of LDS of this wave.
+__device__ __forceinline__ void km_update_group(const KmArgs& a, int bh, int b, int s0, int s1, float* cw) {
+  const int lane = threadIdx.x & 63;
   if (s1 == s0) return;
+  const int32_t* perm = a.perm + (size_t)bh * a.N;
   const float* pts = a.pts + (size_t)bh * a.n * a.R;
   const int R = a.R;
   // loads are unconditional (columns clamped into the row); lanes past R
@@ -1118,24 +1119,41 @@ __global__ __launch_bounds__(256) void k_km_update(KmArgs a, int it) {
   double sum0 = 0.0, sum1 = 0.0;
   auto members = [&](auto two) {
     constexpr bool TWO = decltype(two)::value;
+    constexpr int FL = TWO ? 32 : 64;  // members in flight
+    int nrow = s0 + lane < s1 ? perm[s0 + lane] - a.row0 : 0;
     for (int m0 = s0; m0 < s1; m0 += 64) {
       const int cnt = min(64, s1 - m0);
-      const int myrow = lane < cnt ? perm[m0 + lane] - a.row0 : 0;
-      // 16 members' loads in flight; past the last member the loads read a
-      // member row again and their values are not added
-      for (int u = 0; u < cnt; u += 16) {
-        float v0[16], v1[16];
+      const int myrow = nrow;
+      nrow = m0 + 64 + lane < s1 ? perm[m0 + 64 + lane] - a.row0 : 0;
+      for (int u0 = 0; u0 < cnt; u0 += FL) {
+        float v0[FL], v1[TWO ? FL : 1];
+        // sixteen at a time as far as there are members; past the last one
+        // the loads read a member row again and their values are not added
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const float* pr = pts + (size_t)__builtin_amdgcn_readlane(myrow, (u + e) & 63) * R;
-          v0[e] = pr[k0];
-          if constexpr (TWO) v1[e] = pr[k1];
-        }
+        for (int u = 0; u < FL; u += 16)
+          if (u0 + u < cnt) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e)
-          if (u + e < cnt) {
-            sum0 += (double)v0[e];
-            if constexpr (TWO) sum1 += (double)v1[e];
+            for (int e = 0; e < 16; ++e) {
+              const float* pr = pts + (size_t)__builtin_amdgcn_readlane(myrow, u0 + u + e) * R;
+              v0[u + e] = pr[k0];
+              if constexpr (TWO) v1[u + e] = pr[k1];
+            }
+          }
+#pragma unroll
+        for (int u = 0; u < FL; u += 16)
+          if (u0 + u + 16 <= cnt) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+              sum0 += (double)v0[u + e];
+              if constexpr (TWO) sum1 += (double)v1[u + e];
+            }
+          } else if (u0 + u < cnt) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+              if (u0 + u + e < cnt) {
+                sum0 += (double)v0[u + e];
+                if constexpr (TWO) sum1 += (double)v1[u + e];
+              }
           }
       }
     }
@@ -1152,29 +1170,111 @@ __global__ __launch_bounds__(256) void k_km_update(KmArgs a, int it) {
   // The next assignment's operands of this centroid (as k_km_prep_cent
   // forms them): the hi/lo split of -2c and the squared norm, one fmaf chain
   // in coordinate order through LDS, with its three bf16 parts.
-  __shared__ float cw[4][128];
   const int RP = a.RP;
   uint16_t* hi = a.chi + ((size_t)bh * a.CP + b) * RP;
   uint16_t* lo = a.clo + ((size_t)bh * a.CP + b) * RP;
+  // coordinates past R are zeros, which leave the chain's value as it is
+  cw[lane] = lane < R ? v0 : 0.f;
+  cw[lane + 64] = lane + 64 < R ? v1 : 0.f;
   if (lane < R) {
-    cw[wv][lane] = v0;
     const uint16_t h = bf16_rne_bits(-2.f * v0);
     hi[lane] = h;
     lo[lane] = bf16_rne_bits(-2.f * v0 - bf16_bits_to_f32(h));
   }
   if (lane + 64 < R) {
-    cw[wv][lane + 64] = v1;
     const uint16_t h = bf16_rne_bits(-2.f * v1);
     hi[lane + 64] = h;
     lo[lane + 64] = bf16_rne_bits(-2.f * v1 - bf16_bits_to_f32(h));
   }
   // one wave: its LDS writes land before its reads below
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  float u = 0.f;
+  for (int k = 0; k < R; k += 16) {
+#pragma unroll
+    for (int e = 0; e < 16; e += 4) {
+      const float4 q = *(const float4*)(cw + k + e);
+      u = fmaf(q.x, q.x, u);
+      u = fmaf(q.y, q.y, u);
+      u = fmaf(q.z, q.z, u);
+      u = fmaf(q.w, q.w, u);
+    }
+  }
   if (lane == 0) {
-    float u = 0.f;
-    for (int k = 0; k < R; ++k) u = fmaf(cw[wv][k], cw[wv][k], u);
     a.cu[(size_t)bh * a.CP + b] = u;
     ((uint2*)a.cn3)[(size_t)bh * a.CP + b] = norm_parts(u);
   }
+}
+
+__global__ __launch_bounds__(256) void k_km_update(KmArgs a, int it) {
+  __shared__ __attribute__((aligned(16))) float cw[4][128];
+  const int bh = blockIdx.y, wv = threadIdx.x >> 6;
+  if (km_changed(a, bh)[it] == 0) return;
+  const int b = blockIdx.x * 4 + wv;
+  if (b >= a.C) return;
+  const int32_t* off = a.off + (size_t)bh * a.offstride;
+  km_update_group(a, bh, b, __builtin_amdgcn_readfirstlane(off[b]), __builtin_amdgcn_readfirstlane(off[b + 1]),
+                  cw[wv]);
+}
+
+// The whole stable counting sort of a short sequence by one block of 16 waves
+// per head, and, when there are at most two groups per wave, the centroid
+// update after it (`upd`): the three sort kernels and the update cost a launch
+// each (at least 4.8 us and a 1.9 us gap) 16 times per plan, more than their
+// work on a few thousand rows.  Wave w owns rows [w rpw, (w + 1) rpw); the
+// waves' label counts give each label's total, an exclusive scan the group
+// offsets, and every wave then scatters its rows in order as k_sort_scatter
+// does.
+constexpr int kSmallSortWaves = 16;
+constexpr int kSmallSortRows = 8192;
+
+__host__ __device__ __forceinline__ int small_sort_lds(int C) {
+  // per-wave slots, slice labels, label totals and the scan's scratch
+  return (kSmallSortWaves * (sort_scatter_cstride(C) + 64) + C + 1 + 17) * (int)sizeof(int);
+}
+
+__global__ __launch_bounds__(1024) void k_sort_small(KmArgs a, int it, int upd) {
+  extern __shared__ __attribute__((aligned(16))) int sm[];
+  __shared__ __attribute__((aligned(16))) float cw[kSmallSortWaves][128];
+  const int cs = sort_scatter_cstride(a.C);
+  const int bh = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  if (km_skip(a, bh, it)) return;
+  int* pos = sm + wv * cs;
+  int* sl = sm + kSmallSortWaves * cs + wv * 64;
+  int* tot = sm + kSmallSortWaves * (cs + 64);
+  const int32_t* lab = a.labels + (size_t)bh * a.N + a.row0;
+  const int rpw = (a.n + kSmallSortWaves * 64 - 1) / (kSmallSortWaves * 64) * 64;
+  const int j0 = min(a.n, wv * rpw), j1 = min(a.n, j0 + rpw);
+  for (int b = lane; b < a.C; b += 64) pos[b] = 0;
+  // the wave's own counts (its LDS accesses complete in program order)
+  for (int j = j0 + lane; j < j1; j += 64) atomicAdd(&pos[lab[j]], 1);
+  __syncthreads();
+  // each label's rows before this wave's, and its total
+  for (int b = tid; b < a.C; b += 1024) {
+    int run = 0;
+#pragma unroll
+    for (int w = 0; w < kSmallSortWaves; ++w) {
+      const int c = sm[w * cs + b];
+      sm[w * cs + b] = run;
+      run += c;
+    }
+    tot[b] = run;
+  }
+  __syncthreads();
+  const int total = block_exclusive_scan(tot, a.C, tot + a.C + 1);
+  if (tid == 0) tot[a.C] = total;
+  __syncthreads();
+  int32_t* off = a.off + (size_t)bh * a.offstride;
+  for (int b = tid; b <= a.C; b += 1024) off[b] = tot[b];
+  for (int b = lane; b < a.C; b += 64) pos[b] += tot[b];
+  int32_t* perm = a.perm + (size_t)bh * a.N;
+  for (int s = j0; s < j1; s += 64) sort_slice(lab, s, j1, lane, pos, sl, perm, a.row0);
+  if (!upd) return;
+  __syncthreads();
+  for (int b = wv; b < a.C; b += kSmallSortWaves)
+    km_update_group(a, bh, b, __builtin_amdgcn_readfirstlane(tot[b]), __builtin_amdgcn_readfirstlane(tot[b + 1]),
+                    cw[wv]);
 }
 
 // The dense-prefix rows (before row0) form the extra last group: label C and
@@ -1199,7 +1299,8 @@ __global__ __launch_bounds__(256) void k_group_mean(const void* x, Geom g, const
                                                     float* mean, int query) {
   // One wave per group; lane l owns channels 2l and 2l + 1.  The members'
   // rows are fetched 64 at a time (lane i holds member m0 + i), their values
-  // loaded eight at a time and added in ascending member order.  Key means
+  // loaded sixteen members at a time and added in ascending member order (the
+  // last few together too: one by one each paid a memory round trip).  Key means
   // come from the K/V head; query means (`query`) are pooled over its G query
   // heads, head by head.
   const int bh = blockIdx.y, wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -1234,20 +1335,26 @@ __global__ __launch_bounds__(256) void k_group_mean(const void* x, Geom g, const
         const int cm = min(64, s1 - m0);
         const int pv = lane < cm ? p[m0 + lane] : 0;
         int i = 0;
-        for (; i + 8 <= cm; i += 8) {
-          float2 v[8];
+        for (; i + 16 <= cm; i += 16) {
+          float2 v[16];
 #pragma unroll
-          for (int u = 0; u < 8; ++u) v[u] = ld2(base, __builtin_amdgcn_readlane(pv, i + u));
+          for (int u = 0; u < 16; ++u) v[u] = ld2(base, __builtin_amdgcn_readlane(pv, i + u));
 #pragma unroll
-          for (int u = 0; u < 8; ++u) {
+          for (int u = 0; u < 16; ++u) {
             s0d += (double)v[u].x;
             s1d += (double)v[u].y;
           }
         }
-        for (; i < cm; ++i) {
-          const float2 v = ld2(base, __builtin_amdgcn_readlane(pv, i));
-          s0d += (double)v.x;
-          s1d += (double)v.y;
+        if (i < cm) {
+          float2 v[16];
+#pragma unroll
+          for (int u = 0; u < 16; ++u) v[u] = ld2(base, __builtin_amdgcn_readlane(pv, (i + u) & 63));
+#pragma unroll
+          for (int u = 0; u < 16; ++u)
+            if (i + u < cm) {
+              s0d += (double)v[u].x;
+              s1d += (double)v[u].y;
+            }
         }
       }
     }
@@ -1944,6 +2051,155 @@ __global__ __launch_bounds__(256) void k_sel_choose(Geom g, Work w, int p) {
   }
 }
 
+// The whole selection of a small route matrix by one block per head: the
+// forced cells, then the radix passes of k_sel_hist and k_sel_choose with the
+// cells' keys and costs in registers, instead of 17 launches whose floor (4.8
+// us and a 1.9 us gap each) is far above their work on a few thousand cells.
+constexpr int kSelSmallCells = 16 * 1024;
+
+__global__ __launch_bounds__(1024) void k_sel_small(Geom g, Work w) {
+  constexpr int KC = kSelSmallCells / 1024;
+  static_assert(kSelBins == 256, "one digit per thread of the first four waves");
+  __shared__ unsigned long long hs[kSelBins];
+  __shared__ long long red[16], wsum[4];
+  __shared__ int redc[16];
+  __shared__ int hit;
+  __shared__ long long st_rem, st_above;
+  __shared__ uint64_t st_prefix, st_bound;
+  __shared__ int st_done;
+  const int bh = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int32_t* oq = w.offq + (size_t)bh * (g.CQt + 1);
+  const int32_t* ok = w.offk + (size_t)bh * (g.CKt + 1);
+  const int32_t* fo = w.forced + (size_t)bh * g.CQ;
+  const float* pr = (g.routing == SPARSEPR_ROUTING_TOP_P ? w.skey : w.prio) + (size_t)bh * g.CQ * g.CK;
+  const unsigned long long cunit = sel_count_unit(g);
+  const int ncell = g.CQ * g.CK;
+  uint64_t key[KC];
+  unsigned long long cost[KC];  // 0: not a candidate
+  long long fc = 0;
+  int fcell = 0;
+#pragma unroll
+  for (int k = 0; k < KC; ++k) {
+    const int i = tid + 1024 * k;
+    key[k] = 0;
+    cost[k] = 0;
+    if (i < ncell) {
+      const int a = i / g.CK, b = i - a * g.CK;
+      const int na = oq[a + 1] - oq[a], nb = ok[b + 1] - ok[b];
+      const int f = fo[a];
+      const unsigned long long c = (unsigned long long)na * (unsigned long long)nb;
+      if (b == f) {
+        fc += (long long)c;
+        ++fcell;
+      } else if (na && nb) {
+        key[k] = cell_key(pr[i], i);
+        cost[k] = c;
+      }
+    }
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    fc += __shfl_xor(fc, o);
+    fcell += __shfl_xor(fcell, o);
+  }
+  if (lane == 0) {
+    red[wv] = fc;
+    redc[wv] = fcell;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    long long forced = 0;
+    int fcells = 0;
+    for (int v = 0; v < 16; ++v) {
+      forced += red[v];
+      fcells += redc[v];
+    }
+    const long long rem = (long long)g.budget - forced;
+    const long long all = (long long)g.NV * (long long)g.NV - forced;
+    st_rem = rem;
+    st_prefix = 0;
+    st_above = 0;
+    st_bound = 0;
+    st_done = rem < 0 ? 3 : (all <= rem ? 1 : 0);
+    int64_t* stats = w.stats + (size_t)bh * 16;
+    stats[ST_FORCED_PAIRS] = forced;
+    stats[ST_FORCED_CELLS] = fcells;
+    if (rem < 0) stats[ST_FLAGS] |= SPARSEPR_FLAG_BUDGET_BELOW_FORCED;
+  }
+  __syncthreads();
+  for (int p = 0; p < kSelPasses; ++p) {
+    if (st_done != 0) break;  // uniform: nothing changes it before the next barrier
+    const int shift = 56 - 8 * p;
+    const uint64_t prefix = st_prefix;
+    const long long above = st_above, rem = st_rem;
+    if (tid < kSelBins) hs[tid] = 0;
+    if (tid == 0) hit = kSelBins;
+    __syncthreads();
+    // the first digit a thread meets is summed in a register (the leading
+    // digits are shared by most cells), the others added to LDS one by one
+    int dA = -1;
+    unsigned long long sA = 0;
+#pragma unroll
+    for (int k = 0; k < KC; ++k) {
+      const bool act = cost[k] != 0 && (p == 0 || (key[k] >> (shift + 8)) == (prefix >> (shift + 8)));
+      if (act) {
+        const int dig = (int)((key[k] >> shift) & 255);
+        if (dA < 0) dA = dig;
+        if (dig == dA)
+          sA += cost[k] + cunit;
+        else
+          atomicAdd(&hs[dig], cost[k] + cunit);
+      }
+    }
+    if (dA >= 0) atomicAdd(&hs[dA], sA);
+    __syncthreads();
+    // as k_sel_choose: thread t < 256 takes digit 255 - t
+    const int dg = kSelBins - 1 - tid;
+    uint64_t raw = 0;
+    long long h = 0, x = 0;
+    if (tid < kSelBins) {
+      raw = hs[dg];
+      h = (long long)(cunit ? (raw & (cunit - 1ull)) : raw);
+      x = h;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const long long y = __shfl_up(x, o);
+        if (lane >= o) x += y;
+      }
+      if (lane == 63) wsum[wv] = x;
+    }
+    __syncthreads();
+    long long cum = above + x;
+    if (tid < kSelBins) {
+      for (int v = 0; v < wv; ++v) cum += wsum[v];
+      if (cum > rem) atomicMin(&hit, tid);
+    }
+    __syncthreads();
+    if (hit == kSelBins) {
+      if (tid == 0) st_done = 1;
+    } else if (tid == hit) {
+      const uint64_t np = prefix | ((uint64_t)dg << shift);
+      st_prefix = np;
+      st_above = cum - h;
+      if (shift == 0) {
+        st_bound = np;
+        st_done = 2;
+      } else if (cunit && (raw >> g.sel_cshift) == 1) {
+        st_bound = np | ((1ull << shift) - 1ull);
+        st_done = 2;
+      }
+    }
+    __syncthreads();
+  }
+  if (tid == 0) {
+    int64_t* st = w.selstate + (size_t)bh * 8;
+    st[SS_REM] = st_rem;
+    st[SS_PREFIX] = (int64_t)st_prefix;
+    st[SS_ABOVE] = st_above;
+    st[SS_BOUND] = (int64_t)st_bound;
+    st[SS_DONE] = st_done;
+  }
+}
+
 // Route matrix over all cells (dense-prefix group included): forced cells,
 // cells above the boundary key, and every cell of the dense-prefix group.
 __global__ __launch_bounds__(256) void k_sel_mark(Geom g, Work w) {
@@ -2458,12 +2714,20 @@ __global__ void k_zero_routed(Geom g, Work w) {
 // Host launchers
 // ---------------------------------------------------------------------------
 
-static void run_sort(const KmArgs& a, int BH, int it, hipStream_t s) {
+// Sorts the rows by label; returns whether it also updated the centroids
+// (asked for by `upd`).
+static bool run_sort(const KmArgs& a, int BH, int it, bool upd, hipStream_t s) {
+  if (a.n <= kSmallSortRows && small_sort_lds(a.C) <= 60 * 1024) {
+    upd = upd && a.C <= 2 * kSmallSortWaves;
+    k_sort_small<<<BH, 1024, small_sort_lds(a.C), s>>>(a, it, upd);
+    return upd;
+  }
   const int shm = (a.C + 1 + 17) * (int)sizeof(int);
   k_sort_hist<<<dim3(a.nblk, BH), 256, a.C * sizeof(int), s>>>(a, it);
   k_sort_scan<<<BH, 1024, shm, s>>>(a, it);
   k_sort_scatter<<<dim3(a.nblk, BH), 256,
                    (size_t)kScatterWaves * (sort_scatter_cstride(a.C) + 64) * sizeof(int), s>>>(a, it);
+  return false;
 }
 
 static void assign_step(const Geom& g, const KmArgs& a, int it, hipStream_t s) {
@@ -2500,8 +2764,7 @@ static void run_kmeans(const Geom& g, const KmArgs& a0, hipStream_t s, bool warm
   const int iters = warm ? g.T_warm : g.T;
   for (int it = 0; it < iters; ++it) {
     assign_step(g, a, it, s);
-    run_sort(a, BH, it, s);
-    k_km_update<<<dim3((a.C + 3) / 4, BH), 256, 0, s>>>(a, it);
+    if (!run_sort(a, BH, it, true, s)) k_km_update<<<dim3((a.C + 3) / 4, BH), 256, 0, s>>>(a, it);
   }
   if (a.row0 > 0) k_prefix_group<<<dim3((a.row0 + 255) / 256, BH), 256, 0, s>>>(a);
 }
@@ -2509,11 +2772,12 @@ static void run_kmeans(const Geom& g, const KmArgs& a0, hipStream_t s, bool warm
 template <int D>
 static void project(const Geom& g, const Work& w, const void* x, const float* F, int R, int query,
                     int rms, float eps, float* phi, hipStream_t s) {
-  const dim3 grid((g.NV + 64 * PROJ_CHUNKS - 1) / (64 * PROJ_CHUNKS), g.BH);
+  const int chunks = row_chunks(g.NV, g.BH);
+  const dim3 grid((g.NV + 64 * chunks - 1) / (64 * chunks), g.BH);
   const int RP = (R + 15) / 16 * 16;
   auto run = [&](auto maxr, auto mf) {
     k_project<D, decltype(maxr)::value, decltype(mf)::value><<<grid, 256, 0, s>>>(
-        x, g, F, R, query, rms, eps, phi, w.stats, w.km_xhi, w.km_xlo, w.km_xn, RP);
+        x, g, F, R, query, rms, eps, phi, w.stats, w.km_xhi, w.km_xlo, w.km_xn, RP, chunks);
   };
   auto by_rank = [&](auto mf) {
     if (R <= 32)
@@ -2585,12 +2849,16 @@ static void plan_d(const Geom& g, const Work& w, const void* q, const void* k, h
     while (np2 < g.CK) np2 <<= 1;
     k_route_topp<<<dim3(g.CQ, BH), 256, (size_t)np2 * 8, s>>>(g, w, np2);
   }
-  k_sel_init<<<BH, 256, 0, s>>>(g, w);
-  // about 2048 blocks over all heads, each taking rows of one head
-  const int gsel = std::max(1, std::min(g.CQ, (2048 + BH - 1) / BH));
-  for (int p = 0; p < kSelPasses; ++p) {
-    k_sel_hist<<<dim3(gsel, BH), 256, 0, s>>>(g, w, p);
-    k_sel_choose<<<BH, 256, 0, s>>>(g, w, p);
+  if ((int64_t)g.CQ * g.CK <= kSelSmallCells) {
+    k_sel_small<<<BH, 1024, 0, s>>>(g, w);
+  } else {
+    k_sel_init<<<BH, 256, 0, s>>>(g, w);
+    // about 2048 blocks over all heads, each taking rows of one head
+    const int gsel = std::max(1, std::min(g.CQ, (2048 + BH - 1) / BH));
+    for (int p = 0; p < kSelPasses; ++p) {
+      k_sel_hist<<<dim3(gsel, BH), 256, 0, s>>>(g, w, p);
+      k_sel_choose<<<BH, 256, 0, s>>>(g, w, p);
+    }
   }
   const int64_t ncell_t = (int64_t)g.CQt * g.CKt;
   const int gmark = (int)std::min<int64_t>(std::max<int64_t>((ncell_t + 4095) / 4096, 1), 512);
@@ -2625,11 +2893,11 @@ void launch_rebuild(const Geom& g, const Work& w, int bh, hipStream_t s) {
   KmArgs ak{nullptr, nullptr, w.labk, w.permk, w.offk, w.blkhist, w.kmstate, g.N, 0, g.N,
             0, g.CKt, g.CKt + 1, g.nsort_blk_full, g.cmax, 0, g.T,
             nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0};
-  run_sort(ak, BH, -1, s);
+  run_sort(ak, BH, -1, false, s);
   KmArgs aq{nullptr, nullptr, w.labq, w.permq, w.offq, w.blkhist, w.kmstate, g.N, 0, g.N,
             0, g.CQt, g.CQt + 1, g.nsort_blk_full, g.cmax, 1, g.T,
             nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0};
-  run_sort(aq, BH, -1, s);
+  run_sort(aq, BH, -1, false, s);
   k_zero_routed<<<BH, 64, 0, s>>>(g, w);
   k_ranges<<<dim3((g.CQt + 3) / 4, BH), 256, 0, s>>>(g, w);
   k_chunks<<<BH, 1024, (g.CQt + 1 + 17) * sizeof(int), s>>>(g, w);

@@ -143,6 +143,16 @@ enum {
   ST_FIT_RANK = 11,
 };
 
+// 64-row chunks per block of the kernels that stage a head's small matrices
+// once per block (projection, correction): eight share the staging, fewer
+// where that leaves the launch short of two blocks per CU (with eight, two
+// heads of 1,024 rows were four blocks: correction 94 us, projection 38).
+inline int row_chunks(int rows, int heads) {
+  int c = 8;
+  while (c > 1 && (int64_t)((rows + 64 * c - 1) / (64 * c)) * heads < 512) c /= 2;
+  return c;
+}
+
 // ---- plan kernels -------------------------------------------------------
 void launch_plan(const Geom& g, const Work& w, const void* q, const void* k, hipStream_t s,
                  bool warm);
