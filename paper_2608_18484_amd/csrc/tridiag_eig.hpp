@@ -8,7 +8,8 @@
 //     registers, reflectors in the rows of V).
 //  2. tri_eigvals: the leading eigenvalues of T by multisection of its Sturm
 //     counts in float (8 or 16 threads per eigenvalue, each counting at one
-//     point of the current bracket), descending.
+//     point of the current bracket), descending; ones closer than that
+//     resolves are told apart in double before their vectors (tri_refine).
 //  3. tri_vectors: for the leading nvec eigenvalues, the twisted
 //     factorisation of T - lambda I in double (stationary and progressive
 //     pivot chains, each vector's two chains in different waves; twist index
@@ -469,6 +470,40 @@ __device__ __forceinline__ double tri_guard(double x, double piv) {
   return fabs(x) < piv ? -piv : x;
 }
 
+// Eigenvalues closer together than the float multisection resolves: the
+// leading n, each searched again by Sturm counts in double in a bracket of
+// 4e-6 of the norm around its float value (whose error is below 4e-7), by
+// groups of 8 lanes, to lamv.  Nine rounds divide the bracket by 4e8.
+template <int D, typename T, int NT>
+__device__ void tri_refine(TriWork<D, T, NT>& tw, int n) {
+  constexpr int G = 8;
+  const int tid = threadIdx.x, t = tid / G, sl = tid % G;
+  if (t >= n) return;  // whole groups
+  const int j = D - 1 - t;
+  const double piv = tw.pivd, w = 2e-6 * (double)tw.fnorm;
+  double a = (double)tw.lamf[t] - w, b = (double)tw.lamf[t] + w;
+  for (int rnd = 0; rnd < 9; ++rnd) {
+    const double h = (b - a) / (G + 1);
+    const double x = fma((double)(sl + 1), h, a);
+    double q = tri_guard<D>(tw.d[0] - x, piv);
+    int cnt = q < 0.0;
+#pragma unroll 8
+    for (int i = 0; i < D - 1; ++i) {
+      q = tri_guard<D>((tw.d[i + 1] - x) - tw.e[i] * (tw.e[i] * tri_rcp(q)), piv);
+      cnt += q < 0.0;
+    }
+    const int below = cnt <= j;  // lambda_j >= x
+    int u = 0;
+#pragma unroll
+    for (int o = 0; o < G; ++o) u += __shfl(below, (tid & ~(G - 1)) + o);
+    const double na = u == 0 ? a : fma((double)u, h, a);
+    const double nb = u == G ? b : fma((double)(u + 1), h, a);
+    a = na;
+    b = fmax(nb, na);
+  }
+  if (sl == 0) tw.lamv[t] = 0.5 * (a + b);
+}
+
 // One chain of the twisted factorisation of T - lam I for vector t: the
 // stationary pivots dp (top down, `fwd`) or the progressive pivots dm
 // (bottom up).  scr holds [2][D][D] doubles (dp, dm), entry (i, t) at
@@ -608,13 +643,31 @@ __device__ void tri_vectors(TriWork<D, T, NT>& tw, T* VT, int LV, int nvec, doub
   }
   __syncthreads();
   const double tn = fmax((double)tw.fnorm, DBL_MIN);
-  // a correction of size c leaves the vector about c / gap of its neighbours
-  double conv = 0.0;
-  if (t8 < nvec) {
+  // distance to the neighbouring eigenvalues
+  auto gap_of = [&](auto* lam) {
     double gap = tn;
-    if (t8 > 0) gap = fmin(gap, (double)tw.lamf[t8 - 1] - (double)tw.lamf[t8]);
-    if (t8 + 1 < D) gap = fmin(gap, (double)tw.lamf[t8] - (double)tw.lamf[t8 + 1]);
+    if (t8 > 0) gap = fmin(gap, (double)lam[t8 - 1] - (double)lam[t8]);
+    if (t8 + 1 < D) gap = fmin(gap, (double)lam[t8] - (double)lam[t8 + 1]);
+    return gap;
+  };
+  double conv = 0.0;
+  if constexpr (!SEQ) {
+    // a correction that starts nearer to another eigenvalue converges to that
+    // one: closer ones are told apart first
+    double gap = t8 < nvec ? gap_of(tw.lamf) : tn;
+    if (s8 == 0 && !(gap >= 4e-6 * tn)) tw.again = 1;
+    __syncthreads();
+    const bool close = tw.again;
+    __syncthreads();
+    if (close) {
+      tri_refine<D, T, NT>(tw, min(nvec + 1, D));
+      if (tid == 0) tw.again = 0;
+      __syncthreads();
+      if (t8 < nvec) gap = gap_of(tw.lamv);
+    }
+    // a correction of size c leaves the vector about c / gap of its neighbours
     conv = sizeof(T) == 4 ? fmax(1e-7 * gap, 1e-14 * tn) : fmax(1e-12 * gap, 4e-15 * tn);
+    __syncthreads();
   }
   T* row = VT + (size_t)t8 * LV;
   constexpr int NE = D / 8;
