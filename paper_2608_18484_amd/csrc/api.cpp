@@ -121,7 +121,7 @@ void describe(const Geom& g, Work* w, Layout& L) {
   addq(&w->fitv, 3 * dv * 4);
   addq(&w->fity, dv * r * 4);
   addq(&w->fitpsi, dv * r * 4);
-  addq(&w->fitscr, (2 * M * dv + dv * r + M) * 8);
+  addq(&w->fitscr, (2 * M * dv + M) * 8);
   addq(&w->fitgram, 3 * dv * dv * 8);
   addq(&w->fitvec, (!g.bf16 && dv > 64) ? dv * (dv + 4) * 8 : 0);
   addq(&w->eigscr, 2 * std::max(d, dv) * std::max(d, dv) * 8);

@@ -27,20 +27,18 @@ namespace sparsepr {
 // so Y = B_lambda Psi and the correction of row i is xbar_i Y Psi^T + mu_R.
 // ---------------------------------------------------------------------------
 
-// Per-head scratch of the fit: xbar [M][D], rbar [M][D], rhs [D][r], w~ [M]
-// (all double).
+// Per-head scratch of the fit: xbar [M][D], rbar [M][D], w~ [M] (all double).
 struct FitScratch {
-  double *xb, *rb, *rhs, *wt;
+  double *xb, *rb, *wt;
 };
 
 __device__ __forceinline__ FitScratch fit_scratch(const Geom& g, const Work& w, int bh) {
-  const size_t D = g.dv, M = g.M, r = g.r;
-  double* base = w.fitscr + (size_t)bh * (2 * M * D + D * r + M);
+  const size_t D = g.dv, M = g.M;
+  double* base = w.fitscr + (size_t)bh * (2 * M * D + M);
   FitScratch f;
   f.xb = base;
   f.rb = f.xb + M * D;
-  f.rhs = f.rb + M * D;
-  f.wt = f.rhs + D * r;
+  f.wt = f.rb + M * D;
   return f;
 }
 
@@ -136,8 +134,8 @@ __global__ __launch_bounds__(1024) void k_fit_prep(Geom g, Work w) {
 // which = 0: H = Rbar^T W Rbar (its eigenvectors are the right singular
 // vectors of W^1/2 Rbar, eq. app_probe_residual_basis); which = 1:
 // S = xbar^T W xbar + lambda I (eq. app_ridge_closed_form); which = 2:
-// Rbar^T W xbar, so that the solve's right-hand side xbar^T W (Rbar Psi) is
-// one D x D x r product instead of two passes over the probes in its block.
+// xbar^T W Rbar, the right-hand side of the ridge solve before the projection
+// onto the residual subspace.
 template <int D>
 __global__ __launch_bounds__(256) void k_fit_gram(Geom g, Work w) {
   constexpr int PB = 64;
@@ -148,8 +146,8 @@ __global__ __launch_bounds__(256) void k_fit_gram(Geom g, Work w) {
   if (np == 0) return;
   const int ti = blockIdx.x / (D / 32), tj = blockIdx.x % (D / 32);
   const FitScratch f = fit_scratch(g, w, bq);
-  const double* srca = which == 1 ? f.xb : f.rb;
-  const double* srcb = which == 0 ? f.rb : f.xb;
+  const double* srca = which == 0 ? f.rb : f.xb;
+  const double* srcb = which == 1 ? f.xb : f.rb;
   const int li = tid / 8, lj = (tid % 8) * 4;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
   for (int p0 = 0; p0 < np; p0 += PB) {
@@ -177,30 +175,27 @@ __global__ __launch_bounds__(256) void k_fit_gram(Geom g, Work w) {
   }
 }
 
-// S Y = B for a symmetric positive definite D x D S and r right-hand sides,
-// all double, by one block of 1024 threads: S = L diag(d) L^T by right-looking
+// X = S^-1 B for a symmetric positive definite S, S, B and X D x D in double
+// (X over B), by one block of 1024 threads: S = L diag(d) L^T by right-looking
 // elimination on the augmented matrix [S | B], which lives in registers
-// (thread = one column x one strip of D / 4 rows; rows i % 4 form a strip).
-// Step j publishes row j (double-buffered, so one barrier per step): by
-// symmetry it is also the column every row subtracts, and scaled by 1 / d_j it
-// is row j of L^T (kept in U, row stride D + 1) and of diag(d)^-1 L^-1 B (kept
-// in Z).  Then L^T Y = Z, one wave per right-hand side.  Returns false (Y
-// untouched) when a pivot is not positive.  The Cholesky factorisation with S
-// in LDS, two barriers per column and separate triangular solves took 256 us
-// of the block at D = 128.
+// (thread = one column x one strip of rows, row i in strip i % 4).  Step j
+// publishes row j (double-buffered, so one barrier per step): by symmetry it
+// is also the column every row subtracts, and scaled by 1 / d_j it is row j of
+// L^T (kept in U, row stride D + 1) and of diag(d)^-1 L^-1 B (kept over B).
+// Then L^T X is solved, one wave per column of B.  Returns false when a pivot
+// is not positive.  (A Cholesky factorisation with S in LDS, two barriers per
+// column and separate triangular solves took 256 us of a block at D = 128.)
 template <int D>
-__device__ __forceinline__ bool fit_spd_solve(const double* __restrict__ Sg, double* __restrict__ Z, int r, int rk, double* U,
-                              float* __restrict__ Y) {
+__device__ __forceinline__ bool fit_spd_solve(const double* __restrict__ Sg, double* __restrict__ B, double* U) {
   constexpr int S = 4, NR = D / S, BK = 8, NB = NR / BK, LU = D + 1;
+  static_assert(2 * S * D <= 1024, "one thread per column and strip");
   typedef double blk __attribute__((ext_vector_type(BK)));
   __shared__ __attribute__((aligned(16))) double rowb[2][2][D];
   const int tid = threadIdx.x, lane = tid & 63;
   const int c = tid % D, strip = __builtin_amdgcn_readfirstlane(tid / D);
   const bool rhs = strip >= S;
   const int s = strip % S;
-  // waves whose columns are all beyond the right-hand sides only meet the
-  // barriers
-  const bool act = strip < 2 * S && (!rhs || __builtin_amdgcn_readfirstlane(c & ~63) < rk);
+  const bool act = strip < 2 * S;  // D = 64: the other waves only meet the barriers
   auto pos = [](int i) { return (i % S) * NR + i / S; };
   blk a[NB];
   if (act) {
@@ -209,12 +204,13 @@ __device__ __forceinline__ bool fit_spd_solve(const double* __restrict__ Sg, dou
 #pragma unroll
       for (int e = 0; e < BK; ++e) {
         const int i = s + S * (bk * BK + e);
-        a[bk][e] = rhs ? (c < rk ? Z[(size_t)i * r + c] : 0.0) : Sg[(size_t)i * D + c];
+        a[bk][e] = (rhs ? B : Sg)[(size_t)i * D + c];
       }
     if (s == 0) rowb[0][rhs][rhs ? c : pos(c)] = a[0][0];
   }
   bool ok = true;
-  for (int j = 0; j < D; ++j) {
+  for (int jj = 0; jj < D; ++jj) {
+    const int j = __builtin_amdgcn_readfirstlane(jj);
     const int cur = j & 1;
     __syncthreads();
     const double* x = rowb[cur][0];
@@ -225,15 +221,15 @@ __device__ __forceinline__ bool fit_spd_solve(const double* __restrict__ Sg, dou
       if (s == j % S) {
         if (!rhs)
           U[j * LU + c] = f;
-        else if (c < rk)
-          Z[(size_t)j * r + c] = f;
+        else
+          B[(size_t)j * D + c] = f;
       }
       const double* xs = x + s * NR;
 #pragma unroll
       for (int bk = 0; bk < NB; ++bk)
         if (S * BK * (bk + 1) > j + 1) {
 #pragma unroll
-          for (int e = 0; e < BK; ++e) a[bk][e] -= xs[bk * BK + e] * f;
+          for (int e = 0; e < BK; ++e) a[bk][e] = fma(-xs[bk * BK + e], f, a[bk][e]);
         }
       if (j + 1 < D && s == (j + 1) % S) {
         const int u = (j + 1) / S;
@@ -250,34 +246,51 @@ __device__ __forceinline__ bool fit_spd_solve(const double* __restrict__ Sg, dou
   }
   __syncthreads();
   if (!ok) return false;  // every thread saw the same pivots
-  constexpr int NU = D / 64;
-  for (int t = tid >> 6; t < rk; t += 1024 / 64) {
-    // lane l holds unknowns l, l + 64; each solved one is subtracted from
-    // the rows above it
-    double y[NU];
+  constexpr int NU = D / 64, CW = D / 16;  // rows per lane, columns per wave
+  const int wv = tid >> 6;
+  // a wave's columns four at a time, lane l holding unknowns l, l + 64 of
+  // each; each solved one is subtracted from the rows above it
+  for (int t0 = wv * CW; t0 < (wv + 1) * CW; t0 += 4) {
+    double y[4][NU];
 #pragma unroll
-    for (int u = 0; u < NU; ++u) y[u] = Z[(size_t)(lane + 64 * u) * r + t];
-#pragma unroll 4
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int u = 0; u < NU; ++u) y[q][u] = B[(size_t)(lane + 64 * u) * D + t0 + q];
+    double nl[NU];  // the next column's entries, one step ahead of their use
+#pragma unroll
+    for (int u = 0; u < NU; ++u) nl[u] = U[(lane + 64 * u) * LU + D - 1];
+#pragma unroll 1
     for (int j = D - 1; j > 0; --j) {
-      const double yj = tri_readlane(NU > 1 && j >= 64 ? y[NU - 1] : y[0], j & 63);
+      double l[NU];
 #pragma unroll
       for (int u = 0; u < NU; ++u) {
-        const int i = lane + 64 * u;
-        const double l = U[i * LU + j];
-        if (i < j) y[u] -= l * yj;
+        l[u] = lane + 64 * u < j ? nl[u] : 0.0;
+        nl[u] = U[(lane + 64 * u) * LU + j - 1];
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const double yj = tri_readlane(NU > 1 && j >= 64 ? y[q][NU - 1] : y[q][0], j & 63);
+#pragma unroll
+        for (int u = 0; u < NU; ++u) y[q][u] = fma(-l[u], yj, y[q][u]);
       }
     }
 #pragma unroll
-    for (int u = 0; u < NU; ++u) Y[(size_t)(lane + 64 * u) * r + t] = (float)y[u];
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int u = 0; u < NU; ++u) B[(size_t)(lane + 64 * u) * D + t0 + q] = y[q][u];
   }
   return true;
 }
 
-// Residual subspace and ridge solve, one block of 1024 threads per head:
-// Psi = leading r eigenvectors of H with sigma > 1e-6 sigma_1 (tridiagonal
-// solver, or cyclic Jacobi in LDS when its check fails); then
-// (xbar^T W xbar + lambda I) Y = xbar^T W (Rbar Psi), so Y = B_lambda Psi and
-// the correction of row i is xbar_i Y Psi^T + mu_R.
+// The fit's two serial solves, side by side (blockIdx.y):
+//  * 1: X = (xbar^T W xbar + lambda I)^-1 xbar^T W Rbar, over the Gram kernel's
+//    third matrix; one after the other with the basis, for the r projected
+//    right-hand sides only, the block took 320 us at D = 128, now as long as
+//    the basis alone;
+//  * 0: Psi = leading r eigenvectors of H with sigma > 1e-6 sigma_1
+//    (tridiagonal solver, or cyclic Jacobi in LDS when its check fails).
+// k_fit_map then forms Y = X Psi = B_lambda Psi, so the correction of row i is
+// xbar_i Y Psi^T + mu_R.
 // T is the eigensolver's precision.  Double A and V of a 128 x 128 problem do not
 // both fit in LDS; V (VG) then lives in the head's global scratch.
 template <int D, typename T>
@@ -295,12 +308,18 @@ __global__ __launch_bounds__(1024) void k_fit_solve(Geom g, Work w) {
   const int np = w.nprobes[bh];
   if (np == 0) return;
   const int r = g.r;
-  float* Y = w.fity + (size_t)bq * D * r;
   float* Psi = w.fitpsi + (size_t)bq * D * r;
-  const FitScratch f = fit_scratch(g, w, bq);
-  const double* H = w.fitgram + (size_t)bq * 3 * D * D;
-  const double* Sg = H + D * D;
-  const double* C = Sg + D * D;
+  double* H = w.fitgram + (size_t)bq * 3 * D * D;
+  int64_t* st = w.stats + (size_t)bh * 16;
+  if (blockIdx.y == 1) {
+    double* X = H + 2 * D * D;
+    if (!fit_spd_solve<D>(H + D * D, X, (double*)smem)) {
+      // no map: the correction is the mean residual
+      for (int e = tid; e < D * D; e += 1024) X[e] = 0.0;
+      if (tid == 0) atomicOr((unsigned long long*)&st[ST_FLAGS], (unsigned long long)SPARSEPR_FLAG_FIT_NOT_PD);
+    }
+    return;
+  }
   T* Am = (T*)smem;
   T* Vm = VG ? (T*)(w.fitvec + (size_t)bq * D * LV) : Am + D * LD;  // transposed (jacobi_eig_lds)
   if (g.ridge_only) {
@@ -377,33 +396,36 @@ __global__ __launch_bounds__(1024) void k_fit_solve(Geom g, Work w) {
     const int row = i / rk, t = i % rk;
     Psi[row * r + t] = (float)Vm[order[t] * LV + row];
   }
-  // rhs = (xbar^T W Rbar) Psi: thread (c, g) takes row c of every
-  // (1024 / D)-th direction, two at a time
-  {
-    constexpr int GT = 1024 / D;
-    const int c = tid % D;
-    for (int t0 = tid / D; t0 < rk; t0 += 2 * GT) {
-      const bool two = t0 + GT < rk;
-      const T* v0 = Vm + order[t0] * LV;
-      const T* v1 = Vm + order[two ? t0 + GT : t0] * LV;
-      double a0 = 0.0, a1 = 0.0;
-#pragma unroll 16
-      for (int e = 0; e < D; ++e) {
-        const double x = C[(size_t)e * D + c];
-        a0 += x * (double)v0[e];
-        a1 += x * (double)v1[e];
-      }
-      f.rhs[(size_t)c * r + t0] = a0;
-      if (two) f.rhs[(size_t)c * r + t0 + GT] = a1;
-    }
-  }
+  if (tid == 0) st[ST_FIT_RANK] = rk;
+}
+
+// Y = X Psi (k_fit_solve), 16 directions per block, in double from the float
+// basis that the correction multiplies by.
+template <int D>
+__global__ __launch_bounds__(1024) void k_fit_map(Geom g, Work w) {
+  constexpr int RS = 16, GT = 1024 / D, TP = RS / GT;  // directions per thread
+  __shared__ float ps[D][RS];
+  const int bq = blockIdx.y, bh = bq % g.BH, tid = threadIdx.x;
+  if (w.nprobes[bh] == 0) return;
+  const int r = g.r, t0 = blockIdx.x * RS;
+  const float* Psi = w.fitpsi + (size_t)bq * D * r;
+  float* Y = w.fity + (size_t)bq * D * r;
+  const double* X = w.fitgram + ((size_t)bq * 3 + 2) * D * D;
+  for (int i = tid; i < D * RS; i += 1024) ps[i / RS][i % RS] = t0 + i % RS < r ? Psi[(i / RS) * r + t0 + i % RS] : 0.f;
   __syncthreads();
-  const bool ok = fit_spd_solve<D>(Sg, f.rhs, r, rk, (double*)smem, Y);
-  if (tid == 0) {
-    int64_t* st = w.stats + (size_t)bh * 16;
-    st[ST_FIT_RANK] = rk;
-    if (!ok) atomicOr((unsigned long long*)&st[ST_FLAGS], (unsigned long long)SPARSEPR_FLAG_FIT_NOT_PD);
+  const int c = tid / GT, q = (tid % GT) * TP;
+  double acc[TP];
+#pragma unroll
+  for (int u = 0; u < TP; ++u) acc[u] = 0.0;
+#pragma unroll 16
+  for (int e = 0; e < D; ++e) {
+    const double x = X[(size_t)c * D + e];
+#pragma unroll
+    for (int u = 0; u < TP; ++u) acc[u] += x * (double)ps[e][q + u];
   }
+#pragma unroll
+  for (int u = 0; u < TP; ++u)
+    if (t0 + q + u < r) Y[(size_t)c * r + t0 + q + u] = (float)acc[u];
 }
 
 // Correction and restore (eq. probe_residual_estimate and
@@ -557,9 +579,10 @@ static void fit_d(const Geom& g, const Work& w0, void* out, hipStream_t s, hipEv
   // float inputs (whose outputs are held to float rounding) get the double
   // solve; bf16 inputs the float one
   if (D <= 64 || !g.bf16)
-    k_fit_solve<D, double><<<BQ, 1024, 0, s>>>(g, w0);
+    k_fit_solve<D, double><<<dim3(BQ, 2), 1024, 0, s>>>(g, w0);
   else
-    k_fit_solve<D, float><<<BQ, 1024, 0, s>>>(g, w0);
+    k_fit_solve<D, float><<<dim3(BQ, 2), 1024, 0, s>>>(g, w0);
+  k_fit_map<D><<<dim3((g.r + 15) / 16, BQ), 1024, 0, s>>>(g, w0);
   if (ev) (void)hipEventRecord(ev[3], s);
   const int chunks = row_chunks(g.N, BQ);
   k_correct<D><<<dim3((g.N + 64 * chunks - 1) / (64 * chunks), BQ), 256, 0, s>>>(g, w0, out, chunks);

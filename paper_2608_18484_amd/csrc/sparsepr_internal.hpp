@@ -119,9 +119,9 @@ struct Work {
   float* fitv;        // [BH][3*dv] mu_x, s_x, mu_r
   float* fity;        // [BH][dv][r] B Psi
   float* fitpsi;      // [BH][dv][r]
-  double* fitscr;     // [BH][2*M*dv + dv*r + M] fit scratch
+  double* fitscr;     // [BH][2*M*dv + M] fit scratch
   double* fitgram;    // (in sparsepr_plan the ratios of the response bases' eigensolves)
-                      // [BH][3][dv][dv] Rbar^T W Rbar, xbar^T W xbar + lambda I and Rbar^T W xbar
+                      // [BH][3][dv][dv] Rbar^T W Rbar, xbar^T W xbar + lambda I and xbar^T W Rbar
   double* fitvec;     // [BH][dv][dv+4] eigenvectors (transposed) of a double fit solve kept out of LDS
   double* eigscr;     // [G][BH][2][D][D] pivots of the tridiagonal eigensolver's twisted factorisations (D = max(d, dv))
   int64_t* stats;     // [BH][16]
