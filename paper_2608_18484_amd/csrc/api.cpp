@@ -106,7 +106,7 @@ void describe(const Geom& g, Work* w, Layout& L) {
   add(&w->rng, (size_t)g.CQt * g.CKt * 8);
   add(&w->keytot, (size_t)g.CQt * 4);
   add(&w->chunks, (size_t)g.nchunk_max * 16);
-  add(&w->nchunks, 4);
+  add(&w->nchunks, kItemClasses * 4);
   add(&w->d2, NV * 4);
   add(&w->probes, M * 4);
   add(&w->pw, M * 4);
@@ -224,7 +224,6 @@ sparsepr_status validate(const sparsepr_shape* s, const sparsepr_params* p, Geom
   g.H = s->heads;
   g.Hkv = hkv;
   g.G = s->heads / hkv;
-  g.gq = 0;
   g.BH = s->batch * hkv;
   g.N = N;
   g.ntext = p->n_dense_prefix;
@@ -262,8 +261,13 @@ sparsepr_status validate(const sparsepr_shape* s, const sparsepr_params* p, Geom
   // the probe rows' cost against all keys is reserved before the cells
   g.budget = (int64_t)std::floor((double)p->target_exec_density * (double)NV * (double)NV) -
              (int64_t)g.M * (int64_t)N;
+  // Sparse-attention items of up to four 32-row sets in three launches per
+  // segment share more of each key copy and leave no wave idle, but every
+  // launch drains on its own: sparse attention of 24 heads of 75,600 rows 28.3
+  // -> 27.3 ms, 32 of 84,480 47.6 -> 44.4, 24 of 46,800 10.8 -> 10.1, 16 of
+  // 61,200 at d = 64 7.2 -> 7.0; 24 of 28,800 4.0 -> 4.4, of 17,160 1.56 -> 1.71.
+  g.classes = g.bf16 && (int64_t)g.BH * g.G * N >= int64_t(14000) * kQTile;
   g.nchunk_max = (N + kQTile - 1) / kQTile + g.CQt;
-  g.nchunk_per_xcd = (g.nchunk_max + 7) / 8;
   g.rpad = (std::max(g.rk, g.rq) + 15) / 16 * 16;
   {
     // Key splits of the exact probe rows.  One split of 2048 keys per block
@@ -432,7 +436,7 @@ sparsepr_status sparsepr_plan_create(const sparsepr_shape* shape, const sparsepr
   p->wq.resize(g.G);
   for (int j = 0; j < g.G; ++j) bind(g, &p->wq[j], p->L, p->base, -1, j);
   // no work item and no probe until a plan exists
-  st = hip_check(hipMemset(p->w.nchunks, 0, sizeof(int32_t) * g.BH), "hipMemset");
+  st = hip_check(hipMemset(p->w.nchunks, 0, sizeof(int32_t) * kItemClasses * g.BH), "hipMemset");
   if (st == SPARSEPR_OK) st = hip_check(hipMemset(p->w.nprobes, 0, sizeof(int32_t) * g.BH), "hipMemset");
   if (st == SPARSEPR_OK) st = hip_check(hipMemset(p->w.stats, 0, sizeof(int64_t) * 16 * g.BH), "hipMemset");
   if (st != SPARSEPR_OK) {

@@ -7,8 +7,9 @@
 //  * the probe-fitted residual fit, correction and restore are launched from
 //    here and live in fit_kernels.hip.
 //
-// Layout of the bf16 attention kernel.  A block of 128 threads (2 waves)
-// owns up to 64 query rows of one query group; each wave owns 32 of them.
+// Layout of the bf16 attention kernel.  A block of NW waves (2, or for large
+// launches 3 and 4) owns up to 32 NW query rows of one query group; each wave
+// owns 32 of them.
 // The scores are formed transposed, S^T = K Q^T, with v_mfma_f32_32x32x16_bf16
 // (A = 32 keys x 16 dims from LDS, B = 16 dims x 32 queries held in
 // registers), so every lane holds scores of ONE query and the online softmax
@@ -54,6 +55,7 @@ struct AttnArgs {
   float* mlst;
   int seg_lo, seg_hi, seg_first, seg_last;
   int heads_per_xcd;  // MODE_SPARSE block order (see k_attn_mfma)
+  int cls;            // MODE_SPARSE: class of work items of this launch
 };
 
 // Where the rows and keys of one block come from.
@@ -71,7 +73,7 @@ template <int MODE>
 __device__ __forceinline__ bool get_work(const Geom& g, const AttnArgs& A, int bh, Work1& w) {
   if (MODE == MODE_SPARSE) {
     const int cx = blockIdx.x;
-    if (cx >= A.nchunks[bh]) return false;
+    if (cx >= A.nchunks[bh * kItemClasses + kItemClasses - 1]) return false;
     const int4 c = A.chunks[(size_t)bh * g.nchunk_max + cx];
     w.a = c.x;
     w.rbase = A.offq[(size_t)bh * (g.CQt + 1) + c.x] + c.y;
@@ -191,8 +193,8 @@ __device__ __forceinline__ float pair_sum(float x) {
 }
 
 // Block-sparse flash attention, bf16 MFMA, fp32 accumulation.
-//  * 128 threads = 2 waves; a block owns up to 64 query rows (32 per wave)
-//    that share one key list: the routed ranges of their query group in the
+//  * NW waves; a block owns up to 32 NW query rows (32 per wave) that share
+//    one key list: the routed ranges of their query group in the
 //    group-major K/V copy (MODE_SPARSE), or a contiguous slice of the original
 //    K/V rows (MODE_PROBE).
 //  * 32-key tiles in LDS filled by direct global->LDS 16-byte loads: one K
@@ -200,52 +202,59 @@ __device__ __forceinline__ float pair_sum(float x) {
 //    operands, and two V buffers, the next tile's V loading while the current
 //    one is computed; the key positions of a tile are computed two tiles
 //    ahead into a ring of three slots.  The 26 KB of LDS and at most 168
-//    registers per lane leave room for six blocks per CU (three waves per
-//    SIMD), which hide each other's latencies better than four.
+//    registers per lane leave room for six blocks of two waves per CU (three
+//    waves per SIMD), which hide each other's latencies better than four.
+//    Blocks of three and four waves have LDS to spare at that occupancy: their
+//    K is double-buffered too and a step has one barrier.
 //  * S^T = K Q^T and O^T += V^T P^T with v_mfma_f32_32x32x16_bf16; V^T
 //    fragments come from the row-major V tile through transposing LDS reads.
 //  * Online softmax in base 2 with lazy rescaling: the running maximum only
 //    moves (and O, l are rescaled) when a tile's maximum exceeds it by 2^8.
-template <int D, int MODE>
-__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_attn_mfma(Geom g, AttnArgs A) {
-  constexpr int KT = 32;
+template <int D, int MODE, int NW = 2>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_attn_mfma(Geom g, AttnArgs A) {
+  constexpr int KT = 32, NT = 64 * NW;
   constexpr int CH = D / 8;                    // 16-byte chunks per row
   constexpr int NKS = D / 16;                  // k-steps of Q K^T
   constexpr int NDB = D / 32;                  // 32-wide blocks of O^T
-  constexpr int LPT = KT * CH / 128;           // 16-byte loads per thread per tensor per tile
+  constexpr int NCP = KT * CH / 64;            // 1 KB copies per tensor per tile,
+  constexpr int LPT = (NCP + NW - 1) / NW;     // at most so many per wave
   constexpr int MAXR = 128;                    // routed ranges of the segment staged in LDS
-  // tiles[0] = K (one buffer), tiles[1..2] = V (double-buffered)
-  __shared__ __attribute__((aligned(1024))) uint16_t tiles[3][KT * D];
+  constexpr bool K2 = NW > 2;                  // K double-buffered
+  // tiles[0] = K (one buffer), tiles[1..2] = V (double-buffered), tiles[3] =
+  // K's second buffer
+  __shared__ __attribute__((aligned(1024))) uint16_t tiles[K2 ? 4 : 3][KT * D];
   __shared__ int spos[3][KT];
   __shared__ int2 srng[MODE == MODE_SPARSE ? MAXR : 1];
 
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 31, h = lane >> 5;
   Work1 w;
-  int bh;
+  int bh, jq;  // K/V head, and which of its G query heads
   const uint16_t* Kp;
   const uint16_t* Vp;
   if (MODE == MODE_SPARSE) {
-    // XCD-aware order: hardware block b runs on XCD b % 8.
-    //  * heads_per_xcd (head count a multiple of 8): grid (8 * nchunk_max,
-    //    BH / 8); XCD x runs every chunk of heads x, x + 8, ... in turn, so
-    //    its L2 only ever holds one head's K/V segment and all of that
-    //    head's query groups reuse it.
-    //  * otherwise: grid (8 * ceil(nchunk_max / 8), BH); XCD x takes the
-    //    contiguous slice [x*per, (x+1)*per) of each head's chunks.
-    int cx;
-    if (A.heads_per_xcd) {
-      bh = blockIdx.y * 8 + (blockIdx.x & 7);
-      cx = blockIdx.x >> 3;
-      if (cx >= A.nchunks[bh]) return;
-    } else {
-      bh = blockIdx.y;
-      const int nch = A.nchunks[bh];
+    // XCD-aware order: hardware block b runs on XCD b % 8, which takes the
+    // items b / 8 of its share in turn, the G query heads of a K/V head one
+    // after the other for each item (they read the same keys).
+    //  * heads_per_xcd (K/V head count a multiple of 8): grid (8 G items, BH / 8);
+    //    XCD x runs every item of K/V heads x, x + 8, ... in turn, so its L2
+    //    only ever holds one head's K/V segment and all of that head's query
+    //    groups reuse it.
+    //  * otherwise: grid (8 G ceil(items / 8), BH); XCD x takes the contiguous
+    //    slice [x*per, (x+1)*per) of each head's items.
+    int cx = blockIdx.x >> 3;
+    jq = cx % g.G;
+    cx /= g.G;
+    bh = A.heads_per_xcd ? blockIdx.y * 8 + (blockIdx.x & 7) : blockIdx.y;
+    const int32_t* ends = A.nchunks + bh * kItemClasses;
+    const int c0 = A.cls > 0 ? ends[A.cls - 1] : 0, nch = ends[A.cls] - c0;
+    if (!A.heads_per_xcd) {
       const int per = (nch + 7) / 8;
-      const int x = blockIdx.x & 7, y = blockIdx.x >> 3;
-      cx = x * per + y;
-      if (y >= per || cx >= nch) return;
+      cx = cx < per ? (int)(blockIdx.x & 7) * per + cx : nch;
     }
+    if (cx >= nch) return;
+    cx += c0;
     const int4 c = A.chunks[(size_t)bh * g.nchunk_max + cx];
     w.a = c.x;
     w.rbase = A.offq[(size_t)bh * (g.CQt + 1) + c.x] + c.y;
@@ -256,14 +265,16 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     Kp = A.kperm + (size_t)bh * g.N * D;
     Vp = A.vperm + (size_t)bh * g.N * D;
   } else {
-    bh = (MODE == MODE_PROBE) ? blockIdx.z : blockIdx.y;
+    bh = blockIdx.z % g.BH;
+    jq = blockIdx.z / g.BH;
     if (!get_work<MODE>(g, A, bh, w)) return;
     const int64_t base = kv_base(g, bh);
     Kp = (const uint16_t*)A.k + base;
     Vp = (const uint16_t*)A.v + base;
   }
   const int64_t ksn = (MODE == MODE_SPARSE) ? D : g.sn;  // row stride of Kp/Vp
-  const uint16_t* Qp = (const uint16_t*)A.q + q_base(g, bh, g.gq);
+  const int bq = jq * g.BH + bh;  // entry of the attend outputs
+  const uint16_t* Qp = (const uint16_t*)A.q + q_base(g, bh, jq);
 
   // query row of this lane and its B operands
   const int qr = wv * 32 + n;
@@ -288,12 +299,12 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   typedef const __attribute__((address_space(1))) int* gptr_int;
   gptr_int grng = nullptr;
   int nr = 0, j0 = 0, nseg = 0;
-  __shared__ int sred[2][3];
+  __shared__ int sred[NW][3];
   if (MODE == MODE_SPARSE) {
     grng = (gptr_int)(A.rng + ((size_t)bh * g.CQt + w.a) * g.CKt);
     nr = A.rng_cnt[(size_t)bh * g.CQt + w.a];
     int below = 0, before_end = 0, keys = 0;
-    for (int i = tid; i < nr; i += 128) {
+    for (int i = tid; i < nr; i += NT) {
       const int2 r = make_int2(grng[2 * i], grng[2 * i + 1]);
       below += (r.x + r.y <= A.seg_lo);
       before_end += (r.x < A.seg_hi);
@@ -308,10 +319,15 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
       sred[wv][2] = keys;
     }
     __syncthreads();
-    j0 = sred[0][0] + sred[1][0];
-    nseg = sred[0][1] + sred[1][1] - j0;
-    w.nkeys = sred[0][2] + sred[1][2];
-    for (int i = tid; i < min(nseg, MAXR); i += 128)
+    w.nkeys = 0;
+#pragma unroll
+    for (int v = 0; v < NW; ++v) {
+      j0 += sred[v][0];
+      nseg += sred[v][1];
+      w.nkeys += sred[v][2];
+    }
+    nseg -= j0;
+    for (int i = tid; i < min(nseg, MAXR); i += NT)
       srng[i] = make_int2(grng[2 * (j0 + i)], grng[2 * (j0 + i) + 1]);
     __syncthreads();
   }
@@ -364,14 +380,15 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     uint32_t voff[LPT];
 #pragma unroll
     for (int u = 0; u < LPT; ++u) {
-      const int inst = wv * LPT + u;
-      const int s = inst * 64 + lane;
+      const int inst = u * NW + wv;  // past NCP (uniform) in a last partial round
+      const int s = (inst < NCP ? inst : 0) * 64 + lane;
       const int key = s / CH, p = s % CH;
       const int c8 = p ^ kv_swz<D>(key);
       voff[u] = (uint32_t)spos[tt % 3][key] * row_bytes + (uint32_t)(c8 * 16);
     }
 #pragma unroll
-    for (int u = 0; u < LPT; ++u) g2lds16s(src, voff[u], dst + (uint32_t)((wv * LPT + u) * 1024));
+    for (int u = 0; u < LPT; ++u)
+      if (NCP % NW == 0 || u * NW + wv < NCP) g2lds16s(src, voff[u], dst + (uint32_t)((u * NW + wv) * 1024));
   };
   const uint32_t kdst = lds_tiles;
   auto vdst = [&](int b) { return lds_tiles + (uint32_t)((1 + b) * KT * D * 2); };
@@ -385,7 +402,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     for (int i = 0; i < 16; ++i) O[db][i] = 0.f;
   if (MODE == MODE_SPARSE && !A.seg_first && qvalid) {
     // resume the running state left by the previous key segment
-    const float* src = A.osp + ((size_t)bh * g.N + qrow) * D;
+    const float* src = A.osp + ((size_t)bq * g.N + qrow) * D;
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -396,7 +413,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
         O[db][i4 * 4 + 2] = v4.z;
         O[db][i4 * 4 + 3] = v4.w;
       }
-    const float* ml = A.mlst + ((size_t)bh * g.N + qrow) * 4;
+    const float* ml = A.mlst + ((size_t)bq * g.N + qrow) * 4;
     m_run = ml[0];
     l_run = ml[1 + h];
   }
@@ -417,7 +434,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   // (no fence): ordering is explicit, each wave waits for its own copies and
   // LDS accesses before a barrier.
   auto step = [&](int t, int vb) {
-    const uint16_t* kt = tiles[0];
+    const uint16_t* kt = tiles[K2 && vb ? 3 : 0];
     const uint16_t* vt = tiles[1 + vb];
     // positions first: the range walk may read global memory, and the wait
     // the compiler puts before its use also covers the copies issued
@@ -426,6 +443,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     __builtin_amdgcn_s_waitcnt(0x3f70);  // vmcnt(0): K(t) and V(t) have landed
     __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
     __builtin_amdgcn_s_barrier();
+    if (K2 && t + 1 < ntile) issue(t + 1, Kp, vb ? kdst : kdst + (uint32_t)(3 * KT * D * 2));
     if (t + 1 < ntile) issue(t + 1, Vp, vdst(1 - vb));
     f32x16 S;
     if (wave_active) {
@@ -438,10 +456,12 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
         S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qreg[ks], S, 0, 0, 0);
       }
     }
-    // every wave's K reads are done before K(t+1) overwrites the buffer
-    __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
-    __builtin_amdgcn_s_barrier();
-    if (t + 1 < ntile) issue(t + 1, Kp, kdst);
+    if (!K2) {
+      // every wave's K reads are done before K(t+1) overwrites the buffer
+      __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+      __builtin_amdgcn_s_barrier();
+      if (t + 1 < ntile) issue(t + 1, Kp, kdst);
+    }
     if (wave_active) {
       // register i holds key (i/4)*8 + h*4 + i%4 of the tile
       float mt = -INFINITY;
@@ -524,7 +544,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   if (!qvalid) return;
   const float l_tot = pair_sum(l_run);
   if (MODE == MODE_PROBE) {
-    float* dst = A.part + (((size_t)bh * g.M + w.tile * 64 + qr) * g.nsplit + w.split) * (D + 2);
+    float* dst = A.part + (((size_t)bq * g.M + w.tile * 64 + qr) * g.nsplit + w.split) * (D + 2);
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -541,7 +561,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     const float inv = 1.f / l_tot;
     if (!A.seg_last) {
       // hand the running state to the next key segment
-      float* dst = A.osp + ((size_t)bh * g.N + qrow) * D;
+      float* dst = A.osp + ((size_t)bq * g.N + qrow) * D;
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -550,11 +570,11 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
           *(float4*)(dst + dv) =
               make_float4(O[db][i4 * 4], O[db][i4 * 4 + 1], O[db][i4 * 4 + 2], O[db][i4 * 4 + 3]);
         }
-      float* ml = A.mlst + ((size_t)bh * g.N + qrow) * 4;
+      float* ml = A.mlst + ((size_t)bq * g.N + qrow) * 4;
       if (h == 0) ml[0] = m_run;
       ml[1 + h] = l_run;
     } else {
-      float* dst = A.osp + ((size_t)bh * g.N + qrow) * D;
+      float* dst = A.osp + ((size_t)bq * g.N + qrow) * D;
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -1051,51 +1071,51 @@ static AttnArgs make_args(const Work* w, const void* q, const void* k, const voi
 template <int D>
 static void attend_d(const Geom& g, const Work* wq, const void* q, const void* k, const void* v,
                      void* out, hipStream_t s, hipEvent_t* ev) {
-  const dim3 gp((g.M + 63) / 64, g.nsplit, g.BH);
-  // query head j of every K/V head: its own Geom (Q and output rows) and
-  // workspace view (attend outputs); the plan and the group-major K/V are shared
-  auto gj = [&](int j) {
-    Geom h = g;
-    h.gq = j;
-    return h;
-  };
+  // every kernel takes all G * BH query heads in one launch (view of query
+  // head 0, whose [G][BH] arrays continue with the other query heads)
+  const int BQ = g.BH * g.G;
+  const AttnArgs a = make_args(&wq[0], q, k, v, out);
   if (g.bf16) {
     constexpr int CH = D / 8;
     k_permute_kv<D><<<dim3((g.N + 256 / CH - 1) / (256 / CH), g.BH), 256, 0, s>>>(
         g, k, v, wq[0].permk, wq[0].kperm, wq[0].vperm);
   }
   if (ev) (void)hipEventRecord(ev[0], s);
-  for (int j = 0; j < g.G && g.bf16; ++j) {
-    const AttnArgs a = make_args(&wq[j], q, k, v, out);
-    {
-      // one launch per key segment, so that all blocks in flight read the same
-      // slice of K/V and it stays in L2
-      for (int sg = 0; sg < g.nseg; ++sg) {
-        AttnArgs as = a;
-        as.seg_lo = (int)((int64_t)g.N * sg / g.nseg);
-        as.seg_hi = (int)((int64_t)g.N * (sg + 1) / g.nseg);
-        as.seg_first = sg == 0;
-        as.seg_last = sg == g.nseg - 1;
-        as.heads_per_xcd = g.BH % 8 == 0;
-        const dim3 grid = as.heads_per_xcd ? dim3(8 * g.nchunk_max, g.BH / 8)
-                                           : dim3(8 * g.nchunk_per_xcd, g.BH);
-        k_attn_mfma<D, MODE_SPARSE><<<grid, 128, 0, s>>>(gj(j), as);
+  if (g.bf16) {
+    // one launch per key segment, so that all blocks in flight read the same
+    // slice of K/V and it stays in L2
+    for (int sg = 0; sg < g.nseg; ++sg) {
+      AttnArgs as = a;
+      as.seg_lo = (int)((int64_t)g.N * sg / g.nseg);
+      as.seg_hi = (int)((int64_t)g.N * (sg + 1) / g.nseg);
+      as.seg_first = sg == 0;
+      as.seg_last = sg == g.nseg - 1;
+      as.heads_per_xcd = g.BH % 8 == 0;
+      // one launch per class of work items; an item of 4 (3) sets has at
+      // least 97 (65) rows
+      auto launch = [&](auto nw, int cls, int most) {
+        constexpr int NW = decltype(nw)::value;
+        as.cls = cls;
+        const dim3 grid = as.heads_per_xcd ? dim3(8 * g.G * most, g.BH / 8)
+                                           : dim3(8 * g.G * ((most + 7) / 8), g.BH);
+        if (most > 0) k_attn_mfma<D, MODE_SPARSE, NW><<<grid, 64 * NW, 0, s>>>(g, as);
+      };
+      if (g.classes) {
+        launch(std::integral_constant<int, 4>{}, 0, g.N / 97);
+        launch(std::integral_constant<int, 3>{}, 1, g.N / 65);
       }
+      launch(std::integral_constant<int, 2>{}, 2, g.nchunk_max);
     }
+  } else {
+    k_attn_f32<D, MODE_SPARSE><<<dim3(g.nchunk_max, BQ), 256, 0, s>>>(g, a);
   }
-  // the fp32 kernels take every query head in one launch
-  const int BQ = g.BH * g.G;
-  const AttnArgs a0 = make_args(&wq[0], q, k, v, out);
-  if (!g.bf16) k_attn_f32<D, MODE_SPARSE><<<dim3(g.nchunk_max, BQ), 256, 0, s>>>(g, a0);
   if (ev) (void)hipEventRecord(ev[1], s);
-  // the kernels below take all G * BH query heads in one launch (view of
-  // query head 0, whose [G][BH] arrays continue with the other query heads)
   if (g.M > 0) {
-    for (int j = 0; j < g.G && g.bf16; ++j) {
-      const AttnArgs a = make_args(&wq[j], q, k, v, out);
-      k_attn_mfma<D, MODE_PROBE><<<gp, 128, 0, s>>>(gj(j), a);
-    }
-    if (!g.bf16) k_attn_f32<D, MODE_PROBE><<<dim3(gp.x, gp.y, BQ), 256, 0, s>>>(g, a0);
+    const dim3 gp((g.M + 63) / 64, g.nsplit, BQ);
+    if (g.bf16)
+      k_attn_mfma<D, MODE_PROBE><<<gp, 128, 0, s>>>(g, a);
+    else
+      k_attn_f32<D, MODE_PROBE><<<gp, 256, 0, s>>>(g, a);
     k_probe_merge<<<dim3(g.M, BQ), 128, 0, s>>>(g, wq[0].part, wq[0].nprobes, wq[0].odp);
   }
   if (ev) (void)hipEventRecord(ev[2], s);

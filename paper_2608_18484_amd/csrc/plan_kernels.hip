@@ -2345,51 +2345,63 @@ __global__ __launch_bounds__(256) void k_ranges(Geom g, Work w) {
   }
 }
 
-// Attention work items: each query group split into tiles of kQTile rows.
+// Attention work items: each query group's 32-row sets split into as few items
+// of at most 4 sets (2 unless g.classes) as there can be, as evenly as they
+// divide.
 __global__ __launch_bounds__(1024) void k_chunks(Geom g, Work w) {
-  // A head's chunks in decreasing order of their group's routed key count
-  // (64 buckets of similar counts, heaviest first; any order inside a
-  // bucket): the attention launches dispatch chunks in list order, so the
-  // blocks left at the end of each launch are the short ones.  Every chunk's
-  // rows and arithmetic are the same in any order.
+  // A head's items class by class (4, 3, then 2 or 1 sets), within a class in
+  // decreasing order of their group's routed key count (64 buckets of similar
+  // counts, heaviest first; any order inside a bucket): the attention
+  // launches dispatch items in list order, so the blocks left at the end of
+  // each launch are the short ones.  Every item's rows and arithmetic are the
+  // same in any order.
   constexpr int NB = 64;
-  __shared__ int bcnt[NB];
-  __shared__ int wmax_s, total_s;
-  extern __shared__ int nch[];  // CQt
+  __shared__ int bcnt[kItemClasses * NB];
+  __shared__ int wmax_s;
   const int bh = blockIdx.x, tid = threadIdx.x;
   const int32_t* oq = w.offq + (size_t)bh * (g.CQt + 1);
   const int32_t* kt = w.keytot + (size_t)bh * g.CQt;
-  if (tid < NB) bcnt[tid] = 0;
+  const int most = g.classes ? 4 : 2;
+  for (int i = tid; i < kItemClasses * NB; i += 1024) bcnt[i] = 0;
   if (tid == 0) wmax_s = 0;
   __syncthreads();
-  for (int a = tid; a < g.CQt; a += 1024) {
-    nch[a] = (oq[a + 1] - oq[a] + kQTile - 1) / kQTile;
-    if (nch[a] > 0) atomicMax(&wmax_s, kt[a]);
-  }
+  for (int a = tid; a < g.CQt; a += 1024)
+    if (oq[a + 1] > oq[a]) atomicMax(&wmax_s, kt[a]);
   __syncthreads();
   const int64_t wmax = wmax_s;
-  auto bucket = [&](int a) { return (int)(((wmax - kt[a]) * NB) / (wmax + 1)); };
+  auto bucket = [&](int a, int sets) {
+    const int cls = min(4 - sets, kItemClasses - 1);
+    return cls * NB + (int)(((wmax - kt[a]) * NB) / (wmax + 1));
+  };
+  // f(rows before the item, its sets)
+  auto items = [&](int na, auto f) {
+    const int sets = (na + 31) / 32, n = (sets + most - 1) / most;
+    for (int i = 0, s0 = 0; i < n; ++i) {
+      const int m = sets / n + (i < sets % n);
+      f(s0 * 32, m);
+      s0 += m;
+    }
+  };
   for (int a = tid; a < g.CQt; a += 1024)
-    if (nch[a] > 0) atomicAdd(&bcnt[bucket(a)], nch[a]);
+    items(oq[a + 1] - oq[a], [&](int, int m) { atomicAdd(&bcnt[bucket(a, m)], 1); });
   __syncthreads();
   if (tid == 0) {
     int run = 0;
-    for (int b = 0; b < NB; ++b) {
+    for (int b = 0; b < kItemClasses * NB; ++b) {
       const int c = bcnt[b];
       bcnt[b] = run;
       run += c;
+      if (b % NB == NB - 1) w.nchunks[bh * kItemClasses + b / NB] = run;
     }
-    total_s = run;
   }
   __syncthreads();
   int4* ch = w.chunks + (size_t)bh * g.nchunk_max;
   for (int a = tid; a < g.CQt; a += 1024) {
-    if (nch[a] == 0) continue;
     const int na = oq[a + 1] - oq[a];
-    int c = atomicAdd(&bcnt[bucket(a)], nch[a]);
-    for (int r0 = 0; r0 < na; r0 += kQTile) ch[c++] = make_int4(a, r0, min(kQTile, na - r0), kt[a]);
+    items(na, [&](int r0, int m) {
+      ch[atomicAdd(&bcnt[bucket(a, m)], 1)] = make_int4(a, r0, min(m * 32, na - r0), kt[a]);
+    });
   }
-  if (tid == 0) w.nchunks[bh] = total_s;
 }
 
 // ---------------------------------------------------------------------------
@@ -2864,7 +2876,7 @@ static void plan_d(const Geom& g, const Work& w, const void* q, const void* k, h
   const int gmark = (int)std::min<int64_t>(std::max<int64_t>((ncell_t + 4095) / 4096, 1), 512);
   k_sel_mark<<<dim3(gmark, BH), 256, 0, s>>>(g, w);
   k_ranges<<<dim3((g.CQt + 3) / 4, BH), 256, 0, s>>>(g, w);
-  k_chunks<<<BH, 1024, (g.CQt + 1 + 17) * sizeof(int), s>>>(g, w);
+  k_chunks<<<BH, 1024, 0, s>>>(g, w);
   // Probes (App. A.2)
   if (g.M > 0) {
     if (g.probe_rule == SPARSEPR_PROBES_STRATIFIED) {
@@ -2900,7 +2912,7 @@ void launch_rebuild(const Geom& g, const Work& w, int bh, hipStream_t s) {
   run_sort(aq, BH, -1, false, s);
   k_zero_routed<<<BH, 64, 0, s>>>(g, w);
   k_ranges<<<dim3((g.CQt + 3) / 4, BH), 256, 0, s>>>(g, w);
-  k_chunks<<<BH, 1024, (g.CQt + 1 + 17) * sizeof(int), s>>>(g, w);
+  k_chunks<<<BH, 1024, 0, s>>>(g, w);
   if (g.M > 0) k_probe_weights<<<BH, 256, 0, s>>>(g, w);
   k_plan_stats<<<BH, 256, 0, s>>>(g, w, 0, g.T);
 }

@@ -13,8 +13,12 @@
 
 namespace sparsepr {
 
-// Attention-kernel query tile: rows of one query group handled by a block.
+// Attention-kernel query tile: rows of one query group handled by a block
+// (large bf16 launches: up to twice as many).
 constexpr int kQTile = 64;
+// Classes of sparse-attention work items, by the 32-row sets of an item: 4, 3,
+// and 2 or 1 (the only class of fp32 items), one launch each.
+constexpr int kItemClasses = 3;
 // Key tile of the attention kernels.
 constexpr int kKTile = 64;
 // Probe-row dense attention: most keys per split (fewer when that leaves the
@@ -29,7 +33,6 @@ constexpr int kSelPasses = 8;
 struct Geom {
   int B, H, BH;           // batch, query heads, batch * K/V heads (one plan each)
   int Hkv, G;             // K/V heads; query heads per K/V head (H = Hkv * G)
-  int gq;                 // attend: which query head of each K/V head's group
   int N, NV, ntext;       // rows, video rows, dense-prefix rows
   int d, dv;              // head dims (equal)
   int rk, rq;             // response ranks, clamped to d
@@ -52,8 +55,8 @@ struct Geom {
   int64_t kvsb, kvsh;     // batch and head strides of K and V
   float rho, ridge, eps_q, eps_x;
   int64_t budget;         // video x video pair budget after the probe reservation
+  int classes;            // items of up to 4 sets, in classes (large launches), else of up to 2
   int nchunk_max;         // attention work items per head (upper bound)
-  int nchunk_per_xcd;     // ceil(nchunk_max / 8): chunks of one head per XCD
   int psplit, nsplit;     // probe attention: keys per split, key splits
   int part_km;            // the splits' partials live in the k-means operands
   int nseg;               // key segments of the sparse attention (one launch each)
@@ -103,8 +106,8 @@ struct Work {
   int32_t* rng_cnt;   // [BH][CQt]
   int2* rng;          // [BH][CQt][CKt]: (start position in perm_kv, length)
   int32_t* keytot;    // [BH][CQt]
-  int4* chunks;       // [BH][nchunk_max]: (a, row start in group, rows, keys)
-  int32_t* nchunks;   // [BH]
+  int4* chunks;       // [BH][nchunk_max]: (a, row start in group, rows, keys), class by class
+  int32_t* nchunks;   // [BH][kItemClasses] end of each class in chunks
   float* d2;          // [BH][NV] probe radial distances
   int32_t* probes;    // [BH][M]
   float* pw;          // [BH][M]
