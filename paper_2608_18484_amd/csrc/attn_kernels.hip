@@ -60,13 +60,13 @@ struct AttnArgs {
 
 // Where the rows and keys of one block come from.
 struct Work1 {
-  int nrows;      // valid query rows (<= 64)
+  int nrows;      // valid query rows (<= 32 NW)
   int nkeys;      // keys in the flat key list
-  int k0;         // MODE_PROBE/DENSE: first key row
+  int k0;         // MODE_PROBE: first key row
   int a;          // MODE_SPARSE: query group
   int rbase;      // MODE_SPARSE: first permutation slot of the rows
   int split;      // MODE_PROBE: split index
-  int tile;       // MODE_PROBE/DENSE: row tile
+  int tile;       // MODE_PROBE: row tile
 };
 
 template <int MODE>

@@ -16,14 +16,15 @@
 namespace sparsepr {
 
 // ---------------------------------------------------------------------------
-// Probe-fitted residual fit (Sec. 4.2; App. A.3), one block of 1024 threads
-// per head:
+// Probe-fitted residual fit (Sec. 4.2; App. A.3), per head: the statistics
+// (k_fit_prep), the three products over the probes (k_fit_gram), the basis
+// beside the ridge solve (k_fit_solve, two blocks) and Y (k_fit_map):
 //   alpha_p = w_p / sum w;  mu_x, mu_R weighted means;
 //   s_x = sqrt(sum alpha (x - mu_x)^2 + eps);  xbar = (x - mu_x)/s_x;
 //   Rbar = R - mu_R;  w~_p = M w_p / sum w;
 //   Psi = leading r eigenvectors of Rbar^T W Rbar (right singular vectors of
 //         W^1/2 Rbar), keeping sigma > 1e-6 sigma_1;
-//   (xbar^T W xbar + lambda I) Y = xbar^T W (Rbar Psi)   (Cholesky),
+//   (xbar^T W xbar + lambda I) X = xbar^T W Rbar,  Y = X Psi,
 // so Y = B_lambda Psi and the correction of row i is xbar_i Y Psi^T + mu_R.
 // ---------------------------------------------------------------------------
 

@@ -167,7 +167,7 @@ void launch_rebuild(const Geom& g, const Work& w, int bh, hipStream_t s);
 // ev[0] before the sparse attention, ev[1] after it, ev[2] after the probe
 // rows, ev[3] after the fit, ev[4] after the correction.  wq[j] (j < G) is the
 // workspace view holding the attend outputs of query head j of every K/V
-// head; each phase runs for the G query heads in turn.
+// head; each phase runs for all G query heads in one launch.
 void launch_attend(const Geom& g, const Work* wq, const void* q, const void* k, const void* v,
                    void* out, hipStream_t s, hipEvent_t* ev = nullptr);
 // Fit, correction and restore after the sparse and probe attention
