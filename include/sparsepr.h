@@ -330,7 +330,7 @@ typedef struct {
   int32_t plan_calls;
   int32_t attend_calls;
   int32_t attn_launches;  /* key segments per attend call (a segment is one
-                             launch, or up to three, one per block size) */
+                             launch, or two, one per block size) */
 } sparsepr_timings;
 
 /* Enable (1) or disable (0) event timing on this handle.  Creating the events

@@ -261,11 +261,15 @@ sparsepr_status validate(const sparsepr_shape* s, const sparsepr_params* p, Geom
   // the probe rows' cost against all keys is reserved before the cells
   g.budget = (int64_t)std::floor((double)p->target_exec_density * (double)NV * (double)NV) -
              (int64_t)g.M * (int64_t)N;
-  // Sparse-attention items of up to four 32-row sets in three launches per
+  // Sparse-attention items of up to three 32-row sets in two launches per
   // segment share more of each key copy and leave no wave idle, but every
-  // launch drains on its own: sparse attention of 24 heads of 75,600 rows 28.3
-  // -> 27.3 ms, 32 of 84,480 47.6 -> 44.4, 24 of 46,800 10.8 -> 10.1, 16 of
-  // 61,200 at d = 64 7.2 -> 7.0; 24 of 28,800 4.0 -> 4.4, of 17,160 1.56 -> 1.71.
+  // launch drains on its own: sparse attention of 24 heads of 75,600 rows 28.2
+  // -> 26.2 ms, of 119,056 71.0 -> 66.7; 32 of 84,480, where a few groups of a
+  // head are routed to nearly every key, 48.8 -> 50.0.  A third launch for items
+  // of four sets was slower there (27.1, 70.1 and 50.6 ms: about 100 items an
+  // XCD, as long as the heaviest of them), but is where the line was measured:
+  // 24 heads of 46,800 10.8 -> 10.1, 16 of 61,200 at d = 64 7.2 -> 7.0; 24 of
+  // 28,800 4.0 -> 4.4, of 17,160 1.56 -> 1.71.
   g.classes = g.bf16 && (int64_t)g.BH * g.G * N >= int64_t(14000) * kQTile;
   g.nchunk_max = (N + kQTile - 1) / kQTile + g.CQt;
   g.rpad = (std::max(g.rk, g.rq) + 15) / 16 * 16;

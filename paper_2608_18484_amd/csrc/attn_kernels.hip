@@ -8,7 +8,7 @@
 //    here and live in fit_kernels.hip.
 //
 // Layout of the bf16 attention kernel.  A block of NW waves (2, or for large
-// launches 3 and 4) owns up to 32 NW query rows of one query group; each wave
+// launches 3) owns up to 32 NW query rows of one query group; each wave
 // owns 32 of them.
 // The scores are formed transposed, S^T = K Q^T, with v_mfma_f32_32x32x16_bf16
 // (A = 32 keys x 16 dims from LDS, B = 16 dims x 32 queries held in
@@ -204,7 +204,7 @@ __device__ __forceinline__ float pair_sum(float x) {
 //    ahead into a ring of three slots.  The 26 KB of LDS and at most 168
 //    registers per lane leave room for six blocks of two waves per CU (three
 //    waves per SIMD), which hide each other's latencies better than four.
-//    Blocks of three and four waves have LDS to spare at that occupancy: their
+//    Blocks of three waves have LDS to spare at that occupancy: their
 //    K is double-buffered too and a step has one barrier.
 //  * S^T = K Q^T and O^T += V^T P^T with v_mfma_f32_32x32x16_bf16; V^T
 //    fragments come from the row-major V tile through transposing LDS reads.
@@ -1091,8 +1091,8 @@ static void attend_d(const Geom& g, const Work* wq, const void* q, const void* k
       as.seg_first = sg == 0;
       as.seg_last = sg == g.nseg - 1;
       as.heads_per_xcd = g.BH % 8 == 0;
-      // one launch per class of work items; an item of 4 (3) sets has at
-      // least 97 (65) rows
+      // one launch per class of work items; an item of 3 sets has at least
+      // 65 rows
       auto launch = [&](auto nw, int cls, int most) {
         constexpr int NW = decltype(nw)::value;
         as.cls = cls;
@@ -1100,11 +1100,8 @@ static void attend_d(const Geom& g, const Work* wq, const void* q, const void* k
                                            : dim3(8 * g.G * ((most + 7) / 8), g.BH);
         if (most > 0) k_attn_mfma<D, MODE_SPARSE, NW><<<grid, 64 * NW, 0, s>>>(g, as);
       };
-      if (g.classes) {
-        launch(std::integral_constant<int, 4>{}, 0, g.N / 97);
-        launch(std::integral_constant<int, 3>{}, 1, g.N / 65);
-      }
-      launch(std::integral_constant<int, 2>{}, 2, g.nchunk_max);
+      if (g.classes) launch(std::integral_constant<int, 3>{}, 0, g.N / 65);
+      launch(std::integral_constant<int, 2>{}, 1, g.nchunk_max);
     }
   } else {
     k_attn_f32<D, MODE_SPARSE><<<dim3(g.nchunk_max, BQ), 256, 0, s>>>(g, a);

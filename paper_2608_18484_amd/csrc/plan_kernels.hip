@@ -2346,10 +2346,10 @@ __global__ __launch_bounds__(256) void k_ranges(Geom g, Work w) {
 }
 
 // Attention work items: each query group's 32-row sets split into as few items
-// of at most 4 sets (2 unless g.classes) as there can be, as evenly as they
+// of at most 3 sets (2 unless g.classes) as there can be, as evenly as they
 // divide.
 __global__ __launch_bounds__(1024) void k_chunks(Geom g, Work w) {
-  // A head's items class by class (4, 3, then 2 or 1 sets), within a class in
+  // A head's items class by class (3, then 2 or 1 sets), within a class in
   // decreasing order of their group's routed key count (64 buckets of similar
   // counts, heaviest first; any order inside a bucket): the attention
   // launches dispatch items in list order, so the blocks left at the end of
@@ -2361,7 +2361,7 @@ __global__ __launch_bounds__(1024) void k_chunks(Geom g, Work w) {
   const int bh = blockIdx.x, tid = threadIdx.x;
   const int32_t* oq = w.offq + (size_t)bh * (g.CQt + 1);
   const int32_t* kt = w.keytot + (size_t)bh * g.CQt;
-  const int most = g.classes ? 4 : 2;
+  const int most = g.classes ? 3 : 2;
   for (int i = tid; i < kItemClasses * NB; i += 1024) bcnt[i] = 0;
   if (tid == 0) wmax_s = 0;
   __syncthreads();
@@ -2370,7 +2370,7 @@ __global__ __launch_bounds__(1024) void k_chunks(Geom g, Work w) {
   __syncthreads();
   const int64_t wmax = wmax_s;
   auto bucket = [&](int a, int sets) {
-    const int cls = min(4 - sets, kItemClasses - 1);
+    const int cls = min(3 - sets, kItemClasses - 1);
     return cls * NB + (int)(((wmax - kt[a]) * NB) / (wmax + 1));
   };
   // f(rows before the item, its sets)

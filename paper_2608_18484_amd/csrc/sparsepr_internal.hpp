@@ -14,11 +14,11 @@
 namespace sparsepr {
 
 // Attention-kernel query tile: rows of one query group handled by a block
-// (large bf16 launches: up to twice as many).
+// (large bf16 launches: up to 96).
 constexpr int kQTile = 64;
-// Classes of sparse-attention work items, by the 32-row sets of an item: 4, 3,
+// Classes of sparse-attention work items, by the 32-row sets of an item: 3,
 // and 2 or 1 (the only class of fp32 items), one launch each.
-constexpr int kItemClasses = 3;
+constexpr int kItemClasses = 2;
 // Key tile of the attention kernels.
 constexpr int kKTile = 64;
 // Probe-row dense attention: most keys per split (fewer when that leaves the
@@ -55,7 +55,7 @@ struct Geom {
   int64_t kvsb, kvsh;     // batch and head strides of K and V
   float rho, ridge, eps_q, eps_x;
   int64_t budget;         // video x video pair budget after the probe reservation
-  int classes;            // items of up to 4 sets, in classes (large launches), else of up to 2
+  int classes;            // items of up to 3 sets, in classes (large launches), else of up to 2
   int nchunk_max;         // attention work items per head (upper bound)
   int psplit, nsplit;     // probe attention: keys per split, key splits
   int part_km;            // the splits' partials live in the k-means operands
