@@ -274,19 +274,25 @@ sparsepr_status validate(const sparsepr_shape* s, const sparsepr_params* p, Geom
   g.nchunk_max = (N + kQTile - 1) / kQTile + g.CQt;
   g.rpad = (std::max(g.rk, g.rq) + 15) / 16 * 16;
   {
-    // Key splits of the exact probe rows.  One split of 2048 keys per block
-    // leaves most of the chip idle for short sequences or few heads, so the
-    // splits halve until the launch has a round of blocks (256 CUs with 2
-    // fp32 or 6 bf16 blocks each) or the splits get as short as a few tiles
-    // per wave.  Their partials then go over the k-means operands, which only
-    // planning uses, as far as those hold them, so the workspace never grows.
+    // Key splits of the exact probe rows.  Splits of 2048 keys leave most of the
+    // chip idle for short sequences or few heads, so they halve until the
+    // launch has 512 fp32 blocks (two per CU) or 384 bf16 blocks, or are as
+    // short as a few tiles per wave.  The bf16 line: launches below it gain
+    // (probe rows of 24 heads of 8,192 rows, 192 blocks, 77 -> 54 us; of 8, 71
+    // -> 29; 12 of 17,160, 216 blocks, 78 -> 56; 6 of 75,600, 444 blocks, not
+    // split, 99), while with a line of 1536 blocks, a full round of six per CU,
+    // 24 heads of 17,160 went from 90 to 102 us, 20 of 36,000 from 127 to 159
+    // and 512 of 1,024 from 81 to 95: as many blocks more, each with its own
+    // prologue, and longer merges.  The partials go over the k-means operands,
+    // which only planning uses, as far as those hold them, so the workspace
+    // never grows.
     const int64_t rows = (int64_t)g.BH * g.G * std::max(g.M, 1);
     const int64_t blocks = (int64_t)g.BH * g.G * ((std::max(g.M, 1) + 63) / 64);
     const int64_t scratch = (int64_t)2 * g.BH * NV * g.rpad * 2;
     auto count = [&](int keys) { return (N + keys - 1) / keys; };
     auto fits = [&](int keys) { return rows * count(keys) * (g.dv + 2) * 4 <= scratch; };
     g.psplit = kProbeSplit;
-    const int64_t want = g.bf16 ? 1536 : 512;
+    const int64_t want = g.bf16 ? 384 : 512;
     const int least = g.bf16 ? 256 : 128;
     while (blocks * count(g.psplit) < want && g.psplit > least && fits(g.psplit / 2)) g.psplit /= 2;
     g.nsplit = count(g.psplit);

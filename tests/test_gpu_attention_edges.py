@@ -70,6 +70,28 @@ def test_probe_rows_and_output_over_short_splits(orc, dtype, grid, m):
         assert rel_l2(r["out"][0, h], out) < tol
 
 
+# a bf16 launch of 384 blocks or more keeps whole 2,048-key splits: with one
+# split a probe row is the dense kernel's row (the same key tiles, maxima and
+# rounded probabilities) up to the division's last float bit, which rarely
+# shows in bf16, while shorter splits round the probabilities against other
+# maxima and move about half of the elements
+def test_probe_rows_of_a_full_launch_are_not_split():
+    from paper_2608_18484_amd import sparsepr as S
+    g = torch.Generator().manual_seed(5)
+    q, k, v = (torch.randn(16, 24, 1024, 128, generator=g).bfloat16().cuda() for _ in range(3))
+    op = S.SparsePR(S.shape_of(q), S.default_params(n_kv_groups=16, n_q_groups=16, n_probes=32,
+                                                    target_exec_density=0.25))
+    op(q, k, v)
+    dense = S.dense_attention(q, k, v)
+    same = total = 0
+    for bh in (0, 100, 383):
+        ex = op.export(bh, fields=["probes", "o_dense_probes"])
+        rows = dense[bh // 24, bh % 24].cpu()[torch.from_numpy(ex["probes"].astype(np.int64))]
+        eq = torch.from_numpy(ex["o_dense_probes"]).bfloat16() == rows
+        same, total = same + int(eq.sum()), total + eq.numel()
+    assert same >= 0.999 * total
+
+
 # the eigensolver's own convergence: a basis of every dimension (d = 64 keeps
 # r_Q = d directions, down to the noise floor's close eigenvalues) comes from
 # the tridiagonal solver, in both precisions, and the fit from few and many
