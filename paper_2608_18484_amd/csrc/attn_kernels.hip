@@ -21,6 +21,7 @@
 // K/V rows are gathered on load through the group-major permutation, so the
 // routed K/V groups are contiguous key ranges without a physical copy.
 #include <hip/hip_runtime.h>
+#include <float.h>
 #include <math.h>
 
 #include <type_traits>
@@ -29,6 +30,11 @@
 #include "sparsepr_internal.hpp"
 
 namespace sparsepr {
+
+// Running maximum before any finite score.  Not -inf: keys whose scores are all
+// -inf (the first tile of a key part or of a key split, say) then add nothing,
+// where (-inf) - (-inf) would turn the rows they share with other keys to NaN.
+constexpr float kNoMax = -FLT_MAX;
 
 enum { MODE_SPARSE = 0, MODE_PROBE = 1, MODE_DENSE = 2 };  // MODE_DENSE: k_attn_f32 only
 
@@ -394,7 +400,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3, 3)))
   auto vdst = [&](int b) { return lds_tiles + (uint32_t)((1 + b) * KT * D * 2); };
 
   const float sl2 = 1.4426950408889634f / sqrtf((float)D);
-  float m_run = -INFINITY, l_run = 0.f;
+  float m_run = kNoMax, l_run = 0.f;
   f32x16 O[NDB];
 #pragma unroll
   for (int db = 0; db < NDB; ++db)
@@ -672,7 +678,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
     }
   };
   const float sl2 = 1.4426950408889634f / sqrtf((float)D);
-  float m_run = -INFINITY, l_run = 0.f, mt = 0.f;
+  float m_run = kNoMax, l_run = 0.f, mt = 0.f;
   f32x16 O[NDB];
 #pragma unroll
   for (int db = 0; db < NDB; ++db)
@@ -867,7 +873,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_f32(Geom g, AttnArgs A) {
   // scores are scaled into base 2 with the softmax scale's own rounding
   const float scale = 1.f / sqrtf((float)D);
   const float l2e = 1.4426950408889634f;
-  float m_run = -INFINITY, l_run = 0.f;
+  float m_run = kNoMax, l_run = 0.f;
   f32x16 O[NDB];
 #pragma unroll
   for (int db = 0; db < NDB; ++db)
@@ -981,7 +987,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_f32(Geom g, AttnArgs A) {
   for (int p = 1; p < nparts; ++p) {
     const float(*src)[64] = red[nsets == 2 ? set : p - 1];
     const float mp = src[NREG][lane], lp = src[NREG + 1][lane];
-    // a part without a tile holds (-inf, 0, 0); part 0 always has one
+    // a part without a finite score holds (kNoMax, 0, 0)
     const float m_new = fmaxf(m_run, mp);
     const float fa = exp2f(m_run - m_new), fb = exp2f(mp - m_new);
     m_run = m_new;

@@ -92,6 +92,47 @@ def test_probe_rows_of_a_full_launch_are_not_split():
     assert same >= 0.999 * total
 
 
+# keys whose scores are all -inf (a channel that no query leaves out) add
+# nothing wherever they lie: the first, a later and the last tile, whole key
+# parts and whole key splits
+def _masked(n, lo, hi, dtype, d, heads):
+    g = torch.Generator().manual_seed(n + d)
+    q, k, v = (torch.randn(1, heads, n, d, generator=g) for _ in range(3))
+    q[..., 0] = q[..., 0].abs() + 0.1
+    k[:, :, lo:hi, 0] = -math.inf
+    return (x.bfloat16() for x in (q, k, v)) if dtype == "bf16" else (q, k, v)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n,lo,hi", [(256, 0, 32), (256, 32, 64), (256, 96, 128), (700, 640, 700)])
+def test_dense_attention_with_keys_at_minus_infinity(dtype, d, n, lo, hi):
+    from paper_2608_18484_amd import sparsepr as S
+    q, k, v = _masked(n, lo, hi, dtype, d, 2)
+    got = S.dense_attention(q.cuda(), k.cuda(), v.cuda()).cpu().double()
+    assert rel_l2(got, _dense64(q, k, v)) < (1e-5 if dtype == "f32" else 2e-2)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("lo", [0, 256])
+def test_attend_with_keys_at_minus_infinity(dtype, d, lo):
+    from paper_2608_18484_amd import sparsepr as S
+    n, c = 1024, 16
+    q, k, v = _masked(n, lo, lo + 256, dtype, d, 1)
+    op = S.SparsePR(S.shape_of(q), S.default_params(n_kv_groups=c, n_q_groups=c, n_probes=32,
+                                                    resid_rank=4, target_exec_density=1.0))
+    lab = (np.arange(n) // 64).astype(np.int32)
+    op.import_plan(0, lab, lab, np.ones((c, c), np.uint8), np.arange(16, n, 32, dtype=np.int32))
+    out = torch.empty_like(q, device="cuda")
+    op.attend(q.cuda(), k.cuda(), v.cuda(), out)
+    ref = _dense64(q, k, v)[0, 0]
+    ex = op.export(0, fields=["o_sparse", "o_dense_probes", "probes"])
+    tol = 1e-5 if dtype == "f32" else 2e-2
+    assert rel_l2(ex["o_dense_probes"], ref[ex["probes"].astype(np.int64)]) < tol
+    assert rel_l2(ex["o_sparse"], ref) < tol
+
+
 # the eigensolver's own convergence: a basis of every dimension (d = 64 keeps
 # r_Q = d directions, down to the noise floor's close eigenvalues) comes from
 # the tridiagonal solver, in both precisions, and the fit from few and many
