@@ -330,7 +330,8 @@ __global__ __launch_bounds__(1024) void k_fit_solve(Geom g, Work w) {
     if (tid == 0) rank_s = D;
     __syncthreads();
   } else {
-    tri_reduce_reg<D, T, 1024>([&](int e) { return (T)H[e]; }, Am, tw);
+    const double scl = tri_scale<D>(H);  // only ratios of the eigenvalues are used
+    tri_reduce_reg<D, T, 1024>([&](int e) { return (T)(scl * H[e]); }, Am, tw);
     tri_eigvals<D, T, 1024>(tw, r + 1);
     if (tid == 0) {
       // rank: the leading t < r with sigma_t > 1e-6 sigma_1.  In double the
@@ -360,7 +361,7 @@ __global__ __launch_bounds__(1024) void k_fit_solve(Geom g, Work w) {
     } else {
       if (tid == 0)
         atomicOr((unsigned long long*)&w.stats[(size_t)bh * 16 + ST_FLAGS], (unsigned long long)SPARSEPR_FLAG_EIG_JACOBI);
-      for (int e = tid; e < D * D; e += 1024) Am[(e / D) * LD + (e % D)] = (T)H[e];
+      for (int e = tid; e < D * D; e += 1024) Am[(e / D) * LD + (e % D)] = (T)(scl * H[e]);
       __syncthreads();
       jacobi_eig_lds<D, T, 1024>(Am, Vm, rot, &flag, sizeof(T) == 8 ? T(1e-12) : T(1e-4));
       if (tid < D) {

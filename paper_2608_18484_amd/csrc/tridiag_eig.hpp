@@ -219,16 +219,21 @@ __device__ void tri_reduce(T* A, TriWork<D, T, NT>& tw) {
   __syncthreads();
 }
 
-// Square root and reciprocal of the reflector's scalars: in float the
-// hardware's root (about 1 ulp: it only places alpha) and a refined
-// reciprocal.
-__device__ __forceinline__ float tri_sqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
-__device__ __forceinline__ double tri_sqrt(double x) { return sqrt(x); }
-__device__ __forceinline__ float tri_inv(float x) {
-  const float r = __builtin_amdgcn_rcpf(x);
-  return fmaf(fmaf(-x, r, 1.f), r, r);
+// Power of two that takes the largest diagonal entry of a positive semidefinite
+// double matrix, and with it every entry, to [1, 2) (1 for a matrix without a
+// positive finite diagonal): the float stages square entries and their
+// rounding noise, which leaves the float range for entries beyond 1e19 and
+// below 1e-12.  Each wave finds it for itself.
+template <int D>
+__device__ __forceinline__ double tri_scale(const double* A) {
+  const int lane = threadIdx.x & 63;
+  double m = 0.0;
+#pragma unroll
+  for (int u = 0; u < D / 64; ++u) m = fmax(m, A[(size_t)(lane + 64 * u) * (D + 1)]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o));
+  return m > 0.0 && m <= DBL_MAX ? ldexp(1.0, -ilogb(m)) : 1.0;
 }
-__device__ __forceinline__ double tri_inv(double x) { return 1.0 / x; }
 
 // Stage 1 with the matrix in registers.  load(e): element e of the D x D symmetric matrix (row-major).
 // Step k takes x = row k right of the diagonal to alpha e_1 by H = I - beta
@@ -239,11 +244,15 @@ __device__ __forceinline__ double tri_inv(double x) { return 1.0 / x; }
 // the strips owning rows k + 1 and k + 2 publish them for the next step: two
 // barriers per step.  Rows and columns up to k are left alone by zeros in
 // x and w.  Waves beyond RW only meet the barriers.
+// A float matrix has its largest entry near 1 (tri_scale).  A row whose
+// squares sum to at most TINY, 1e-15 of that at most and far below its
+// rounding, counts as reduced: beta = 2 / v.v would leave the range of T.
 template <int D, typename T, int NT, class Load>
 __device__ void tri_reduce_reg(Load load, T* V, TriWork<D, T, NT>& tw) {
   using W = TriWork<D, T, NT>;
   constexpr int RW = W::RW, S = W::S, NR = W::NR, U = D / 64;
   constexpr int BK = 8, NB = NR / BK;
+  constexpr T TINY = sizeof(T) == 4 ? T(1e-30) : T(1e-200);
   static_assert(NR % BK == 0, "row blocks");
   typedef T blk __attribute__((ext_vector_type(BK)));
   const int tid = threadIdx.x, lane = tid & 63;
@@ -304,12 +313,12 @@ __device__ void tri_reduce_reg(Load load, T* V, TriWork<D, T, NT>& tw) {
       st = tri_wave_sum(st);
       alpha = x0;
       v0 = x0;
-      if (st > T(0)) {
-        const T nrm = tri_sqrt(fma(x0, x0, st));
+      if (st > TINY) {
+        const T nrm = sqrt(fma(x0, x0, st));
         alpha = x0 >= T(0) ? -nrm : nrm;
         v0 = x0 - alpha;
         // beta = 2 / v.v of the rounded v keeps H orthogonal to rounding
-        b = tri_inv(T(0.5) * fma(v0, v0, st));
+        b = T(1) / (T(0.5) * fma(v0, v0, st));
       }
     }
     __syncthreads();

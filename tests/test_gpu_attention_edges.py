@@ -157,6 +157,29 @@ def test_eigensolver_without_jacobi_and_fit_ranks(orc, dtype, d, rank):
             assert rel_l2(g, fit["g"]) < 1e-4
 
 
+# residuals far from 1: the float solver of the bf16 d = 128 basis squares the
+# entries of Rbar^T W Rbar and of its rounding noise, so V near 1e-5 (noise
+# below the float range) or 1e10 (squares above it) shows whether the matrix is
+# brought into range first; the double ones only meet their float eigenvalue
+# search there
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128)])
+@pytest.mark.parametrize("rank", [1, 16])
+@pytest.mark.parametrize("e", [-40, -30, -20, -17, 31, 36, 45])
+def test_fit_of_small_and_large_values(orc, dtype, d, rank, e):
+    from paper_2608_18484_amd import sparsepr as S
+    from paper_2608_18484_amd import workloads as W
+    wl = medium(grid=(3, 16, 24), heads=1, dtype=dtype, d=d, n_probes=64, resid_rank=rank)
+    q, k, v, _ = W.make_inputs(wl)
+    r = _run(wl, inputs=(q, k, v * np.float32(2.0) ** e))
+    ex = r["op"].export(0)
+    assert ex["fit_rank"] == rank
+    assert not r["op"].stats()["status_flags"] & S.FLAG_EIG_JACOBI
+    ref, _ = _replay(orc, r, ex, 0, 0)
+    # bf16: 2^-9 of the rounded probabilities and as much of the output, where
+    # the correction is 1.4e-2 of it
+    assert rel_l2(r["out"][0, 0], ref) < (1e-5 if dtype == "f32" else 2.0 ** -8)
+
+
 # a ridge matrix that is not positive definite (no ridge, fewer probes than
 # dimensions): the flag is raised and the correction is the mean residual
 @pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 128)])
