@@ -751,32 +751,31 @@ __device__ void tri_vectors(TriWork<D, T, NT>& tw, T* VT, int LV, int nvec, doub
   // each group keeps its vector in registers and meets the later ones
   constexpr int NC = D / 32;  // 4-entry pieces per lane: piece j starts at (8 j + s8) * 4
   typedef T T4 __attribute__((ext_vector_type(4)));
-  const T tol = sizeof(T) == 4 ? T(1e-4) : T(1e-9);
+  const double tol = sizeof(T) == 4 ? 1e-4 : 1e-9;
   bool bad = false;
   if (t8 < nvec) {
     const double lam = tw.lamv[t8];
-    double res = 0.0;
     for (int i = s8; i < D; i += 8) {
       double y = (tw.d[i] - lam) * (double)row[i];
       if (i > 0) y += tw.e[i - 1] * (double)row[i - 1];
       if (i < D - 1) y += tw.e[i] * (double)row[i + 1];
-      res = fmax(res, fabs(y));
+      bad |= !(fabs(y) <= tol * tn);  // NaN too
     }
-    bad = !(res <= (double)tol * tn);
     T4 z[NC];
 #pragma unroll
     for (int j = 0; j < NC; ++j) z[j] = *(const T4*)(row + (8 * j + s8) * 4);
     // from the first vector after the wave's first: uniform over the wave
     for (int b = __builtin_amdgcn_readfirstlane(t8) + 1; b < nvec; ++b) {
       const T* zb = VT + (size_t)b * LV;
-      T dot = 0;
+      double dot = 0.0;
 #pragma unroll
       for (int j = 0; j < NC; ++j) {
         const T4 y = *(const T4*)(zb + (8 * j + s8) * 4);
-        dot += (z[j].x * y.x + z[j].y * y.y) + (z[j].z * y.z + z[j].w * y.w);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dot = fma((double)z[j][e], (double)y[e], dot);
       }
       dot = tri_group_sum<8>(dot);
-      if (b > t8 && !(fabs(dot) <= tol)) bad = true;
+      if (b > t8) bad |= !(fabs(dot) <= tol);
     }
   }
   if (bad) tw.ok = 0;
