@@ -26,10 +26,11 @@
 // Every stage is a serial chain of one block, so latency is what counts:
 //  * tri_reduce takes four barriers per column and one wave forms each
 //    reflector: 231 us at D = 128 (1.8 us per column); tri_reduce_reg two
-//    barriers, 138 us in float and 206 in double (D = 64, double: 65 us);
+//    barriers, 146 us in float and 206 in double (D = 64, double: 65 us);
 //  * the vectors' products, one lane per side and three sweeps over pivots
 //    in global memory, were two thirds of stage 3 (97 us for 64 vectors at
-//    D = 128); formed by all 8 lanes and kept in registers, stage 3 takes 51;
+//    D = 128); formed by all 8 lanes and kept in registers, stage 3 takes
+//    about 60;
 //  * with a fixed two Rayleigh passes, vectors of eigenvalues closer than
 //    about 1e-3 of the largest kept more than 1e-9 of their neighbours, so
 //    that double solves fell back to Jacobi on most inputs (0.93-1.0 ms a
@@ -466,7 +467,8 @@ __device__ void tri_eigvals(TriWork<D, T, NT>& tw, int need) {
 }
 
 // Reciprocal to about 1 ulp: the hardware estimate and two Newton steps, a
-// third of an IEEE division's dependent chain.  Pivots stay within
+// third of an IEEE division's dependent chain, for the Sturm counts of
+// tri_refine, which take only the signs of the pivots.  These stay within
 // [DBL_MIN, 1 / DBL_MIN] in magnitude (tri_guard and the floor's scale).
 __device__ __forceinline__ double tri_rcp(double x) {
   double r = __builtin_amdgcn_rcp(x);
@@ -516,7 +518,7 @@ __device__ void tri_refine(TriWork<D, T, NT>& tw, int n) {
 // One chain of the twisted factorisation of T - lam I for vector t: the
 // stationary pivots dp (top down, `fwd`) or the progressive pivots dm
 // (bottom up).  scr holds [2][D][D] doubles (dp, dm), entry (i, t) at
-// i * D + t, so that each wave's accesses are contiguous.  SEQ divides and
+// i * D + t, so that each wave's accesses are contiguous.  SEQ also
 // keeps the ratios rho_i = e_i / dp_i and sig_i = e_i / dm_{i+1} in rat
 // ([2][D][D], the same layout).
 template <int D, bool SEQ, typename T, int NT>
@@ -529,7 +531,7 @@ __device__ void tri_chain(const TriWork<D, T, NT>& tw, double lam, double* __res
     sdp[t] = dp;
 #pragma unroll 8
     for (int i = 0; i < D - 1; ++i) {
-      const double rho = SEQ ? tw.e[i] / dp : tw.e[i] * tri_rcp(dp);
+      const double rho = tw.e[i] / dp;
       if (SEQ) rat[i * D + t] = rho;
       dp = tri_guard<D>((tw.d[i + 1] - lam) - tw.e[i] * rho, piv);
       sdp[(i + 1) * D + t] = dp;
@@ -540,7 +542,7 @@ __device__ void tri_chain(const TriWork<D, T, NT>& tw, double lam, double* __res
     sdm[(D - 1) * D + t] = dm;
 #pragma unroll 8
     for (int i = D - 2; i >= 0; --i) {
-      const double sig = SEQ ? tw.e[i] / dm : tw.e[i] * tri_rcp(dm);
+      const double sig = tw.e[i] / dm;
       if (SEQ) rat[D * D + i * D + t] = sig;
       dm = tri_guard<D>((tw.d[i] - lam) - tw.e[i] * sig, piv);
       sdm[i * D + t] = dm;
@@ -599,7 +601,7 @@ __device__ double tri_twisted(const TriWork<D, T, NT>& tw, const double* __restr
   for (int u = 0; u < NE; ++u) {
     const int i = i0 + u;
     const double e = tw.e[i < r ? i : (i > r ? i - 1 : 0)];
-    z[u] = i == r ? 1.0 : -e * tri_rcp(z[u]);
+    z[u] = i == r ? 1.0 : -e / z[u];
   }
   // products within the lane: downwards for the entries after r, upwards for
   // those before it (entry r is 1 in both)
@@ -637,7 +639,7 @@ __device__ double tri_twisted(const TriWork<D, T, NT>& tw, const double* __restr
 // SEQ only).  The two pivot
 // chains of a factorisation run in different waves; the twist search, the
 // vector's products and the checks use a group of 8 lanes per vector.
-// SEQ: IEEE divisions, the products one after another in two lanes, and
+// SEQ: the products one after another in two lanes, and
 // exactly one correction.
 template <int D, bool SEQ, typename T, int NT>
 __device__ void tri_vectors(TriWork<D, T, NT>& tw, T* VT, int LV, int nvec, double* scr, double* rat) {
