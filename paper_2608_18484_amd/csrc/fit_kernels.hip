@@ -394,26 +394,29 @@ __global__ __launch_bounds__(1024) void k_fit_solve(Geom g, Work w) {
     __syncthreads();
   }
   const int rk = rank_s;
-  for (int i = tid; i < D * rk; i += 1024) {
-    const int row = i / rk, t = i % rk;
-    Psi[row * r + t] = (float)Vm[order[t] * LV + row];
+  // Psi for the correction in float; k_fit_map takes it as solved, in double,
+  // over H, which is done with
+  for (int i = tid; i < D * r; i += 1024) {
+    const int row = i / r, t = i % r;
+    const double p = t < rk ? (double)Vm[order[t] * LV + row] : 0.0;
+    H[i] = p;
+    if (t < rk) Psi[i] = (float)p;
   }
   if (tid == 0) st[ST_FIT_RANK] = rk;
 }
 
-// Y = X Psi (k_fit_solve), 16 directions per block, in double from the float
-// basis that the correction multiplies by.
+// Y = X Psi (both from k_fit_solve) in double, 16 directions per block.
 template <int D>
 __global__ __launch_bounds__(1024) void k_fit_map(Geom g, Work w) {
   constexpr int RS = 16, GT = 1024 / D, TP = RS / GT;  // directions per thread
-  __shared__ float ps[D][RS];
+  __shared__ double ps[D][RS];
   const int bq = blockIdx.y, bh = bq % g.BH, tid = threadIdx.x;
   if (w.nprobes[bh] == 0) return;
   const int r = g.r, t0 = blockIdx.x * RS;
-  const float* Psi = w.fitpsi + (size_t)bq * D * r;
   float* Y = w.fity + (size_t)bq * D * r;
-  const double* X = w.fitgram + ((size_t)bq * 3 + 2) * D * D;
-  for (int i = tid; i < D * RS; i += 1024) ps[i / RS][i % RS] = t0 + i % RS < r ? Psi[(i / RS) * r + t0 + i % RS] : 0.f;
+  const double* Psi = w.fitgram + (size_t)bq * 3 * D * D;
+  const double* X = Psi + 2 * D * D;
+  for (int i = tid; i < D * RS; i += 1024) ps[i / RS][i % RS] = t0 + i % RS < r ? Psi[(i / RS) * r + t0 + i % RS] : 0.0;
   __syncthreads();
   const int c = tid / GT, q = (tid % GT) * TP;
   double acc[TP];
@@ -423,7 +426,7 @@ __global__ __launch_bounds__(1024) void k_fit_map(Geom g, Work w) {
   for (int e = 0; e < D; ++e) {
     const double x = X[(size_t)c * D + e];
 #pragma unroll
-    for (int u = 0; u < TP; ++u) acc[u] += x * (double)ps[e][q + u];
+    for (int u = 0; u < TP; ++u) acc[u] += x * ps[e][q + u];
   }
 #pragma unroll
   for (int u = 0; u < TP; ++u)

@@ -123,8 +123,9 @@ struct Work {
   float* fity;        // [BH][dv][r] B Psi
   float* fitpsi;      // [BH][dv][r]
   double* fitscr;     // [BH][2*M*dv + M] fit scratch
-  double* fitgram;    // (in sparsepr_plan the ratios of the response bases' eigensolves)
-                      // [BH][3][dv][dv] Rbar^T W Rbar, xbar^T W xbar + lambda I and xbar^T W Rbar
+  double* fitgram;    // [BH][3][dv][dv] Rbar^T W Rbar, xbar^T W xbar + lambda I and xbar^T W Rbar,
+                      // then Psi [dv][r] over the first and the ridge map over the third; in
+                      // sparsepr_plan the ratios of the response bases' eigensolves
   double* fitvec;     // [BH][dv][dv+4] eigenvectors (transposed) of a double fit solve kept out of LDS
   double* eigscr;     // [G][BH][2][D][D] pivots of the tridiagonal eigensolver's twisted factorisations (D = max(d, dv))
   int64_t* stats;     // [BH][16]

@@ -180,6 +180,33 @@ def test_fit_of_small_and_large_values(orc, dtype, d, rank, e):
     assert rel_l2(r["out"][0, 0], ref) < (1e-5 if dtype == "f32" else 2.0 ** -8)
 
 
+# the fit's map keeps the double basis up to its only rounding: Y is the float
+# nearest to the fp64 solution on the same sparse and probe rows (a basis
+# rounded to float first moves a fifth of the elements by a float step)
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("rank", [1, 8])
+def test_fit_map_is_rounded_once(d, rank):
+    from paper_2608_18484_amd import workloads as W
+    wl = medium(grid=(4, 16, 24), heads=1, dtype="f32", d=d, n_probes=300, resid_rank=rank,
+                density=0.4)
+    q, k, v, _ = W.make_inputs(wl)
+    v = np.random.default_rng(1).standard_normal(v.shape).astype(np.float32)
+    r = _run(wl, inputs=(q, k, v))
+    ex = r["op"].export(0)
+    x = ex["o_sparse"].astype(np.float64)[ex["probes"]]
+    res = ex["o_dense_probes"].astype(np.float64) - x
+    w = ex["probe_weights"].astype(np.float64)
+    m, al = len(w), (w / w.sum())[:, None]
+    mx = (al * x).sum(0)
+    xb = (x - mx) / np.sqrt((al * (x - mx) ** 2).sum(0) + float(np.float32(1e-6)))
+    rb = res - (al * res).sum(0)
+    psi = np.linalg.eigh(rb.T @ (m * al * rb))[1][:, ::-1][:, :rank]
+    y = np.linalg.solve(xb.T @ (m * al * xb) + float(np.float32(wl.ridge)) * np.eye(d),
+                        xb.T @ (m * al * (rb @ psi)))
+    y *= np.sign((psi * ex["fit_psi"]).sum(0))
+    assert np.mean(ex["fit_bpsi"] == y.astype(np.float32)) > 0.99
+
+
 # a ridge matrix that is not positive definite (no ridge, fewer probes than
 # dimensions): the flag is raised and the correction is the mean residual
 @pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 128)])
