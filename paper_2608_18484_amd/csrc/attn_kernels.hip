@@ -145,6 +145,12 @@ __device__ __forceinline__ int kv_swz(int r) {
   return ((r & 3) << 1) | ((r >> 2) & 1);
 }
 
+// Vectors in memory that is only as aligned as its elements: the callers' fp32
+// rows and outputs (a base pointer need not be aligned further) and the probe
+// partials' rows of D + 2 floats.  gfx950 moves them by the same wide accesses.
+typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x2_u __attribute__((ext_vector_type(2), aligned(2)));
+
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) v4i16 lds_v4i16;
 
@@ -556,8 +562,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3, 3)))
 #pragma unroll
       for (int i4 = 0; i4 < 4; ++i4) {
         const int dv = db * 32 + i4 * 8 + h * 4;
-        *(float4*)(dst + dv) =
-            make_float4(O[db][i4 * 4], O[db][i4 * 4 + 1], O[db][i4 * 4 + 2], O[db][i4 * 4 + 3]);
+        *(f32x4_u*)(dst + dv) =
+            f32x4_u{O[db][i4 * 4], O[db][i4 * 4 + 1], O[db][i4 * 4 + 2], O[db][i4 * 4 + 3]};
       }
     if (h == 0) {
       dst[D] = m_run;
@@ -793,7 +799,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
         const uint16_t hi = __builtin_bit_cast(uint16_t, (__bf16)(O[db][i4 * 4 + e + 1] * inv));
         o[e >> 1] = (uint32_t)lo | ((uint32_t)hi << 16);
       }
-      *(uint2*)(dst + dv) = make_uint2(o[0], o[1]);
+      *(u32x2_u*)(dst + dv) = u32x2_u{o[0], o[1]};
     }
 }
 
@@ -841,7 +847,7 @@ template <int D, int MODE>
 __global__ __launch_bounds__(256, 2) void k_attn_f32(Geom g, AttnArgs A) {
   constexpr int KT = 32, NQ = D / 8, HQ = NQ / 2, NDB = D / 32;
   constexpr int NREG = 16 * NDB;
-  typedef float fv __attribute__((ext_vector_type(NDB)));
+  typedef float fv __attribute__((ext_vector_type(NDB), aligned(4)));
   __shared__ float red[3][NREG + 2][64];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -860,9 +866,9 @@ __global__ __launch_bounds__(256, 2) void k_attn_f32(Geom g, AttnArgs A) {
   const int qr = set * 32 + n;
   const bool qvalid = qr < w.nrows;
   const int qrow = row_of<MODE>(g, A, bh, w, qvalid ? qr : 0);
-  float4 q4[NQ];
+  f32x4_u q4[NQ];
 #pragma unroll
-  for (int j = 0; j < NQ; ++j) q4[j] = *(const float4*)(Qp + (int64_t)qrow * g.sn + 8 * j + 4 * h);
+  for (int j = 0; j < NQ; ++j) q4[j] = *(const f32x4_u*)(Qp + (int64_t)qrow * g.sn + 8 * j + 4 * h);
   const int2* rg = nullptr;
   int nr = 0;
   if (MODE == MODE_SPARSE) {
@@ -884,12 +890,12 @@ __global__ __launch_bounds__(256, 2) void k_attn_f32(Geom g, AttnArgs A) {
   auto tile_row = [&](int t) {
     return key_row<MODE>(g, A, bh, w, min(t * KT + n, w.nkeys - 1), cur, rg, nr);
   };
-  float4 ka[HQ], kb[HQ];
+  f32x4_u ka[HQ], kb[HQ];
   fv va[8], vb[8];
-  auto load_k = [&](float4* dst, int row, int half) {
+  auto load_k = [&](f32x4_u* dst, int row, int half) {
     const float* src = Kp + (int64_t)row * g.sn + 4 * h + half * (HQ * 8);
 #pragma unroll
-    for (int j = 0; j < HQ; ++j) dst[j] = *(const float4*)(src + 8 * j);
+    for (int j = 0; j < HQ; ++j) dst[j] = *(const f32x4_u*)(src + 8 * j);
   };
   auto load_v = [&](fv* dst, int row, int half) {
 #pragma unroll
@@ -900,10 +906,10 @@ __global__ __launch_bounds__(256, 2) void k_attn_f32(Geom g, AttnArgs A) {
     }
   };
   f32x16 S;
-  auto scores = [&](const float4* kk, int half) {
+  auto scores = [&](const f32x4_u* kk, int half) {
 #pragma unroll
     for (int j = 0; j < HQ; ++j) {
-      const float4 q = q4[half * HQ + j];
+      const f32x4_u q = q4[half * HQ + j];
       S = __builtin_amdgcn_mfma_f32_32x32x2f32(kk[j].x, q.x, S, 0, 0, 0);
       S = __builtin_amdgcn_mfma_f32_32x32x2f32(kk[j].y, q.y, S, 0, 0, 0);
       S = __builtin_amdgcn_mfma_f32_32x32x2f32(kk[j].z, q.z, S, 0, 0, 0);

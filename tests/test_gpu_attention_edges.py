@@ -52,6 +52,30 @@ def test_dense_attention_block_orders(d, batch, heads, kv, n):
     assert rel_l2(got[:, :, rows], ref) < 2e-2
 
 
+# base pointers aligned only to an element: fp32 Q, K, V and output, and a bf16
+# output, one element into their allocation
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_attention_one_element_into_an_allocation(dtype, d):
+    from paper_2608_18484_amd import sparsepr as S
+    g = torch.Generator().manual_seed(d)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    q, k, v = (torch.randn(1, 2, 513, d, generator=g).to(dt).cuda() for _ in range(3))
+
+    def shifted(t):
+        return torch.empty(t.numel() + 1, dtype=dt, device="cuda")[1:].view(t.shape).copy_(t)
+
+    inputs = [shifted(x) for x in (q, k, v)] if dtype == "f32" else (q, k, v)
+    assert torch.equal(S.dense_attention(*inputs, out=shifted(q)), S.dense_attention(q, k, v))
+    if dtype == "f32":
+        p = S.default_params(n_kv_groups=9, n_q_groups=9, n_probes=70, target_exec_density=0.5)
+        outs = []
+        for x in (inputs, (q, k, v)):
+            op = S.SparsePR(S.shape_of(q), p)
+            outs.append(op(*x, out=torch.empty_like(q)))
+        assert torch.equal(*outs)
+
+
 # probe rows over key splits: the last split short, one and two tiles of
 # probes, more splits than the shortest split allows at this length
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
