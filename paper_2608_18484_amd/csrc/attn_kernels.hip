@@ -1149,12 +1149,17 @@ static void dense_d(const Geom& g, const AttnArgs& a, hipStream_t s) {
   // Four waves share a tile's copies when such blocks fill the chip twice
   // over (24 heads of 17,160 rows: 3.52 ms, with two waves 3.91); shorter
   // launches spread over twice the blocks (2 heads of 1,275 rows: 29.7 us,
-  // with four waves 31.2; 12 of 4,335 at d = 64: 92 us either way).
+  // with four waves 31.2; 12 of 4,335 at d = 64: 92 us either way), and so do
+  // heads of one or three 64-row tiles, half or a quarter of whose 128-row
+  // blocks would be padding (d = 128, two waves and four: 2,400 heads of 33
+  // rows 22.3 and 27.1 us, 600 of 130 23.7 and 32.0, 1,200 of 192 51.6 and
+  // 61.3; with five tiles either may win: 200 of 300 20.6 and 26.8, 768 of 300
+  // 72.6 and 68.0).
   const int64_t heads = (int64_t)g.BH * g.G, blocks4 = (g.N + 127) / 128 * heads;
-  if (blocks4 >= 512)
+  if (blocks4 >= 512 && tiles != 1 && tiles != 3)
     k_attn_dense<D, 4><<<(unsigned)blocks4, 256, 0, s>>>(g, a);
   else
-    k_attn_dense<D, 2><<<(unsigned)((g.N + 63) / 64 * heads), 128, 0, s>>>(g, a);
+    k_attn_dense<D, 2><<<(unsigned)(tiles * heads), 128, 0, s>>>(g, a);
 }
 
 void launch_dense(const Geom& g, const void* q, const void* k, const void* v, void* out,
