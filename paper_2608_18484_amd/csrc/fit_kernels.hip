@@ -580,14 +580,16 @@ static void fit_d(const Geom& g, const Work& w0, void* out, hipStream_t s, hipEv
   // arrays continue with the other query heads)
   const int BQ = g.BH * g.G;
   k_fit_prep<D><<<BQ, 1024, 0, s>>>(g, w0);
-  k_fit_gram<D><<<dim3((D / 32) * (D / 32), 3, BQ), 256, 0, s>>>(g, w0);
-  // float inputs (whose outputs are held to float rounding) get the double
-  // solve; bf16 inputs the float one
-  if (D <= 64 || !g.bf16)
-    k_fit_solve<D, double><<<dim3(BQ, 2), 1024, 0, s>>>(g, w0);
-  else
-    k_fit_solve<D, float><<<dim3(BQ, 2), 1024, 0, s>>>(g, w0);
-  k_fit_map<D><<<dim3((g.r + 15) / 16, BQ), 1024, 0, s>>>(g, w0);
+  if (g.M > 0) {  // without probes the statistics are all of the fit
+    k_fit_gram<D><<<dim3((D / 32) * (D / 32), 3, BQ), 256, 0, s>>>(g, w0);
+    // float inputs (whose outputs are held to float rounding) get the double
+    // solve; bf16 inputs the float one
+    if (D <= 64 || !g.bf16)
+      k_fit_solve<D, double><<<dim3(BQ, 2), 1024, 0, s>>>(g, w0);
+    else
+      k_fit_solve<D, float><<<dim3(BQ, 2), 1024, 0, s>>>(g, w0);
+    k_fit_map<D><<<dim3((g.r + 15) / 16, BQ), 1024, 0, s>>>(g, w0);
+  }
   if (ev) (void)hipEventRecord(ev[3], s);
   const int chunks = row_chunks(g.N, BQ);
   k_correct<D><<<dim3((g.N + 64 * chunks - 1) / (64 * chunks), BQ), 256, 0, s>>>(g, w0, out, chunks);
