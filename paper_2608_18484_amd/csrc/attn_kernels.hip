@@ -389,12 +389,19 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3, 3)))
   // the copies of tile tt of one tensor into the buffer at dst
   auto issue = [&](int tt, const uint16_t* src, uint32_t dst) {
     // all positions first (one LDS wait), then the copies
+    // Two waves: keys at a constant distance from the lane's first, so that one
+    // register addresses the positions (with keys from the scalar wave index
+    // the loop held an address per copy and read them one by one: 28.45 -> 28.27
+    // ms for the sparse attention of 24 heads of 75,600 rows).  Three waves,
+    // whose last round is partial, are faster by the wave index (with classes
+    // 25.3 ms, this way 25.7).
     uint32_t voff[LPT];
 #pragma unroll
     for (int u = 0; u < LPT; ++u) {
       const int inst = u * NW + wv;  // past NCP (uniform) in a last partial round
       const int s = (inst < NCP ? inst : 0) * 64 + lane;
-      const int key = s / CH, p = s % CH;
+      const int key = NW == 2 ? tid / CH + u * (NT / CH) : s / CH;
+      const int p = NW == 2 ? tid % CH : s % CH;
       const int c8 = p ^ kv_swz<D>(key);
       voff[u] = (uint32_t)spos[tt % 3][key] * row_bytes + (uint32_t)(c8 * 16);
     }
