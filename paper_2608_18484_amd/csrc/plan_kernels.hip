@@ -2351,56 +2351,73 @@ __global__ __launch_bounds__(256) void k_ranges(Geom g, Work w) {
 __global__ __launch_bounds__(1024) void k_chunks(Geom g, Work w) {
   // A head's items class by class (3, then 2 or 1 sets), within a class in
   // decreasing order of their group's routed key count (64 buckets of similar
-  // counts, heaviest first; any order inside a bucket): the attention
-  // launches dispatch items in list order, so the blocks left at the end of
-  // each launch are the short ones.  Every item's rows and arithmetic are the
-  // same in any order.
-  constexpr int NB = 64;
-  __shared__ int bcnt[kItemClasses * NB];
+  // counts, heaviest first; any order of the groups inside a bucket): the
+  // attention launches dispatch items in list order, so the blocks left at the
+  // end of each launch are the short ones.  A group's items of a class follow
+  // each other and so read its keys together: placed one by one, between those
+  // of other groups, two-wave blocks took 28.34 ms instead of 28.17 for the
+  // sparse attention of 24 heads of 75,600 rows and 1,368 us instead of 1,354
+  // for 24 of 17,160.  Every item's rows and arithmetic are the same in any
+  // order.
+  constexpr int NB = 64, NBK = kItemClasses * NB;
+  static_assert(NBK == 128, "two buckets per lane of one wave");
+  __shared__ int bcnt[NBK];
   __shared__ int wmax_s;
-  const int bh = blockIdx.x, tid = threadIdx.x;
+  const int bh = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
   const int32_t* oq = w.offq + (size_t)bh * (g.CQt + 1);
   const int32_t* kt = w.keytot + (size_t)bh * g.CQt;
   const int most = g.classes ? 3 : 2;
-  for (int i = tid; i < kItemClasses * NB; i += 1024) bcnt[i] = 0;
+  for (int i = tid; i < NBK; i += 1024) bcnt[i] = 0;
   if (tid == 0) wmax_s = 0;
   __syncthreads();
   for (int a = tid; a < g.CQt; a += 1024)
     if (oq[a + 1] > oq[a]) atomicMax(&wmax_s, kt[a]);
   __syncthreads();
   const int64_t wmax = wmax_s;
-  auto bucket = [&](int a, int sets) {
-    const int cls = min(3 - sets, kItemClasses - 1);
-    return cls * NB + (int)(((wmax - kt[a]) * NB) / (wmax + 1));
+  auto bucket = [&](int a) { return (int)(((wmax - kt[a]) * NB) / (wmax + 1)); };
+  // a group's items: `big` of `sets / n + 1` sets, then the others of one less
+  struct Split {
+    int n, big, small;  // items, items of the larger size, sets of the smaller
   };
-  // f(rows before the item, its sets)
-  auto items = [&](int na, auto f) {
+  auto split = [&](int na) {
     const int sets = (na + 31) / 32, n = (sets + most - 1) / most;
-    for (int i = 0, s0 = 0; i < n; ++i) {
-      const int m = sets / n + (i < sets % n);
-      f(s0 * 32, m);
-      s0 += m;
-    }
+    return n > 0 ? Split{n, sets % n, sets / n} : Split{0, 0, 0};
   };
-  for (int a = tid; a < g.CQt; a += 1024)
-    items(oq[a + 1] - oq[a], [&](int, int m) { atomicAdd(&bcnt[bucket(a, m)], 1); });
+  // items of the first class (3 sets) among them; they lead
+  auto first = [&](const Split& x) { return x.small == 3 ? x.n : (x.small == 2 && most == 3 ? x.big : 0); };
+  for (int a = tid; a < g.CQt; a += 1024) {
+    const Split x = split(oq[a + 1] - oq[a]);
+    const int f = first(x);
+    if (f > 0) atomicAdd(&bcnt[bucket(a)], f);
+    if (x.n > f) atomicAdd(&bcnt[NB + bucket(a)], x.n - f);
+  }
   __syncthreads();
-  if (tid == 0) {
-    int run = 0;
-    for (int b = 0; b < kItemClasses * NB; ++b) {
-      const int c = bcnt[b];
-      bcnt[b] = run;
-      run += c;
-      if (b % NB == NB - 1) w.nchunks[bh * kItemClasses + b / NB] = run;
+  if (tid < 64) {
+    // exclusive scan of the buckets, two per lane: lanes 0-31 hold class 0
+    const int c0 = bcnt[2 * lane], c1 = bcnt[2 * lane + 1];
+    int x = c0 + c1;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(x, o);
+      if (lane >= o) x += y;
     }
+    bcnt[2 * lane] = x - c0 - c1;
+    bcnt[2 * lane + 1] = x - c1;
+    if (lane % (NB / 2) == NB / 2 - 1) w.nchunks[bh * kItemClasses + lane / (NB / 2)] = x;
   }
   __syncthreads();
   int4* ch = w.chunks + (size_t)bh * g.nchunk_max;
   for (int a = tid; a < g.CQt; a += 1024) {
     const int na = oq[a + 1] - oq[a];
-    items(na, [&](int r0, int m) {
-      ch[atomicAdd(&bcnt[bucket(a, m)], 1)] = make_int4(a, r0, min(m * 32, na - r0), kt[a]);
-    });
+    const Split x = split(na);
+    const int f = first(x);
+    int c = f > 0 ? atomicAdd(&bcnt[bucket(a)], f) : 0;
+    for (int i = 0, s0 = 0; i < x.n; ++i) {
+      if (i == f) c = atomicAdd(&bcnt[NB + bucket(a)], x.n - f);
+      const int m = x.small + (i < x.big);
+      ch[c++] = make_int4(a, s0 * 32, min(m * 32, na - s0 * 32), kt[a]);
+      s0 += m;
+    }
   }
 }
 
