@@ -263,14 +263,22 @@ sparsepr_status validate(const sparsepr_shape* s, const sparsepr_params* p, Geom
              (int64_t)g.M * (int64_t)N;
   // Sparse-attention items of up to three 32-row sets in two launches per
   // segment share more of each key copy and leave no wave idle, but every
-  // launch drains on its own: sparse attention of 24 heads of 75,600 rows 28.2
-  // -> 26.2 ms, of 119,056 71.0 -> 66.7; 32 of 84,480, where a few groups of a
-  // head are routed to nearly every key, 48.8 -> 50.0.  A third launch for items
-  // of four sets was slower there (27.1, 70.1 and 50.6 ms: about 100 items an
-  // XCD, as long as the heaviest of them), but is where the line was measured:
-  // 24 heads of 46,800 10.8 -> 10.1, 16 of 61,200 at d = 64 7.2 -> 7.0; 24 of
-  // 28,800 4.0 -> 4.4, of 17,160 1.56 -> 1.71.
-  g.classes = g.bf16 && (int64_t)g.BH * g.G * N >= int64_t(14000) * kQTile;
+  // launch drains on its own, and with few items of three sets per head an XCD
+  // runs several heads at once and holds all their keys.  Sparse attention
+  // without and with classes: 24 heads of 75,600 rows 27.9 and 25.9 ms, of
+  // 37,440 6.77 and 6.56, 32 of 28,800 5.26 and 5.16, 96 of 17,160 5.66 and
+  // 5.45, 80 of 14,000 3.13 and 3.10; 24 of 28,800 3.85 and 3.89, 40 of 24,000
+  // 4.46 and 4.58, 64 of 14,000 2.46 and 2.57, 256 of 8,192 3.27 and 3.33, 445
+  // of 2,048 0.87 and 1.14.  Where the K/V heads are no multiple of 8 the XCDs
+  // take slices of each head's items and the heaviest slice counts (12 of 75,600
+  // 24.3 and 21.1 ms, 43 of 24,000 8.97 and 8.49, 67 of 14,000 4.56 and 4.41;
+  // 133 of 8,192 3.36 and 3.87).  Routes do not enter the rule: where a few
+  // groups of a head are routed to nearly every key and its key work lies less
+  // in items of three sets (27% against 40%; 32 heads of 84,480) classes take
+  // 49.6 ms and one launch 48.9.
+  const int64_t rows64 = (int64_t)g.BH * g.G * N / kQTile;
+  g.classes = g.bf16 && N >= 14000 &&
+              (rows64 >= 17000 || (rows64 >= 14000 && (N >= 28000 || g.BH % 8 != 0)));
   g.nchunk_max = (N + kQTile - 1) / kQTile + g.CQt;
   g.rpad = (std::max(g.rk, g.rq) + 15) / 16 * 16;
   {
