@@ -234,14 +234,27 @@ def test_fit_map_is_rounded_once(d, rank):
     assert np.mean(ex["fit_bpsi"] == y.astype(np.float32)) > 0.99
 
 
-# a ridge matrix that is not positive definite (no ridge, fewer probes than
-# dimensions): the flag is raised and the correction is the mean residual
-@pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 128)])
-def test_fit_not_positive_definite(dtype, d):
+# a ridge matrix that is not positive definite: a channel of V that is zero
+# leaves its row and column of the unregularised matrix exactly zero, whatever
+# the other pivots are (noise with fewer probes than dimensions, positive with
+# more).  The flag is raised and the correction is the mean residual.
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128)])
+@pytest.mark.parametrize("probes,channel", [(9, 0), (200, 0), (200, 37), (200, -1)])
+def test_fit_not_positive_definite(dtype, d, probes, channel):
     from paper_2608_18484_amd import sparsepr as S
-    wl = medium(grid=(2, 16, 24), heads=1, dtype=dtype, d=d, n_probes=9, resid_rank=4, ridge=0.0)
-    r = _run(wl)
+    from paper_2608_18484_amd import workloads as W
+    wl = medium(grid=(2, 16, 24), heads=1, dtype=dtype, d=d, n_probes=probes, resid_rank=4,
+                density=0.5, ridge=0.0)
+    q, k, v, _ = W.make_inputs(wl)
+    v[..., channel] = 0.0
+    r = _run(wl, inputs=(q, k, v))
+    assert r["op"].stats()["status_flags"] & S.FLAG_FIT_NOT_PD
     ex = r["op"].export(0)
-    if r["op"].stats()["status_flags"] & S.FLAG_FIT_NOT_PD:
-        assert np.all(ex["fit_bpsi"] == 0.0)
-    assert np.isfinite(r["out"]).all() or not r["op"].stats()["status_flags"] & S.FLAG_FIT_NOT_PD
+    assert np.all(ex["fit_bpsi"] == 0.0)
+    out = r["out"][0, 0]
+    assert np.isfinite(out).all()
+    ref = ex["o_sparse"] + ex["fit_mu_r"]
+    ref[ex["probes"]] = ex["o_dense_probes"]
+    if dtype == "bf16":
+        ref = torch.from_numpy(ref).bfloat16().float().numpy()
+    assert np.array_equal(out, ref)
