@@ -253,8 +253,8 @@ sparsepr_status sparsepr_workspace_size(const sparsepr_shape* shape, const spars
  * n_kv * stride_n * element size of 4 GiB or more (one head's K/V rows are
  * addressed with 32-bit byte offsets).
  * Tuning: the bf16 sparse attention runs in key segments of about 6 MiB of
- * one head's group-major K+V each (one launch per segment, sized for one
- * XCD's L2); the environment variable SPARSEPR_SEG_KB, read here, overrides
+ * one head's group-major K+V each (one or two launches per segment, sized for
+ * one XCD's L2); the environment variable SPARSEPR_SEG_KB, read here, overrides
  * that size in KiB (at least 64).  The result is the same up to the fp32
  * rounding of the regrouped tiles. */
 sparsepr_status sparsepr_plan_create(const sparsepr_shape* shape, const sparsepr_params* params,
@@ -291,8 +291,9 @@ sparsepr_status sparsepr_plan(sparsepr_plan_t plan, const void* q, const void* k
 sparsepr_status sparsepr_attend(sparsepr_plan_t plan, const void* q, const void* k,
                                 const void* v, void* out, void* stream);
 
-/* Dense attention of Sec. 3 (eq. dense_attention) for every head, on the same
- * kernels the probes use; for error reporting.  Needs no plan, allocates
+/* Dense attention of Sec. 3 (eq. dense_attention) for every head: in bf16 a kernel
+ * of its own, in fp32 the one the probes use; for error reporting and layers
+ * that stay dense.  Needs no plan, allocates
  * nothing; `workspace` must hold sparsepr_dense_workspace_size bytes. */
 sparsepr_status sparsepr_dense_workspace_size(const sparsepr_shape* shape, size_t* bytes);
 sparsepr_status sparsepr_dense_attend(const sparsepr_shape* shape, const void* q, const void* k,

@@ -70,8 +70,6 @@ void describe(const Geom& g, Work* w, Layout& L) {
   };
   add(&w->gram_k, d * d * 8);
   add(&w->gram_q, d * d * 8);
-  add(&w->evals_k, d * 4);
-  add(&w->evals_q, d * 4);
   add(&w->fk, d * g.rk * 4);
   add(&w->fq, d * g.rq * 4);
   add(&w->phik, NV * g.rk * 4);
@@ -145,8 +143,7 @@ void bind(const Geom& g, Work* w, const Layout& L, char* base, int bh, int j = 0
   }
   // the probe partials of attend, flat over [G][BH], in the k-means operands
   // km_xhi and km_xlo (adjacent; only sparsepr_plan uses them)
-  if (g.part_km)
-    w->part = (float*)w->km_xhi + (size_t)j * g.BH * std::max(g.M, 1) * g.nsplit * (g.dv + 2);
+  if (g.part_km) w->part = (float*)w->km_xhi;
 }
 
 sparsepr_status validate(const sparsepr_shape* s, const sparsepr_params* p, Geom& g) {
@@ -337,7 +334,6 @@ sparsepr_status validate(const sparsepr_shape* s, const sparsepr_params* p, Geom
 struct sparsepr_plan_s {
   Geom g;
   Work w;                // whole-batch view (attend outputs of query head 0 of each group)
-  std::vector<Work> wq;  // the same with the attend outputs of query head j, j < G
   Layout L;
   char* base;
   size_t bytes;
@@ -451,8 +447,6 @@ sparsepr_status sparsepr_plan_create(const sparsepr_shape* shape, const sparsepr
   p->base = (char*)workspace;
   p->bytes = bytes;
   bind(g, &p->w, p->L, p->base, -1);
-  p->wq.resize(g.G);
-  for (int j = 0; j < g.G; ++j) bind(g, &p->wq[j], p->L, p->base, -1, j);
   // no work item and no probe until a plan exists
   st = hip_check(hipMemset(p->w.nchunks, 0, sizeof(int32_t) * kItemClasses * g.BH), "hipMemset");
   if (st == SPARSEPR_OK) st = hip_check(hipMemset(p->w.nprobes, 0, sizeof(int32_t) * g.BH), "hipMemset");
@@ -501,7 +495,7 @@ sparsepr_status sparsepr_attend(sparsepr_plan_t plan, const void* q, const void*
     }
     ev = plan->ev_att[plan->n_att++];
   }
-  launch_attend(plan->g, plan->wq.data(), q, k, v, out, (hipStream_t)stream, ev);
+  launch_attend(plan->g, plan->w, q, k, v, out, (hipStream_t)stream, ev);
   const sparsepr_status st = hip_check(hipGetLastError(), "sparsepr_attend launch");
   if (st != SPARSEPR_OK) return st;
   return ok();

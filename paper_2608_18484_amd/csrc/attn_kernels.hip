@@ -1,7 +1,7 @@
 // Attention-side kernels of the SparsePR operator for gfx950:
 //  * renormalised hard-drop block-sparse attention over the routed cells
 //    (Sec. 3 eq. hard_drop; Sec. 4.3), bf16 MFMA with fp32 accumulation, or
-//    an fp32 VALU variant;
+//    an fp32 MFMA variant;
 //  * exact probe rows against all keys (Sec. 4.3; App. A.2 eq.
 //    app_probe_residual), split over keys and merged by log-sum-exp;
 //  * the probe-fitted residual fit, correction and restore are launched from
@@ -163,20 +163,10 @@ __device__ __forceinline__ v4i16 lds_read_tr16(const uint16_t* p) {
 }
 
 // Direct global->LDS copy of 16 bytes per lane: lane l's bytes land at
-// lds_base + 16*l (lds_base must be the same for the whole wave).  Issued as
-// inline assembly so that the compiler adds no waits for it; callers order it
-// with explicit s_waitcnt vmcnt.  Nothing else in these kernels uses M0.
-__device__ __forceinline__ void g2lds16(const void* src, const void* lds_base) {
-  const uint32_t lds = __builtin_amdgcn_readfirstlane(
-      (uint32_t)(size_t)(const __attribute__((address_space(3))) void*)lds_base);
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-               :
-               : "v"(src), "s"(lds)
-               : "memory");
-}
-
-// The same copy addressed as a uniform 64-bit base (SGPRs) plus a 32-bit
-// per-lane byte offset; `m0v` is the wave-uniform LDS destination.
+// m0v + 16*l, m0v being the wave-uniform LDS address, from a uniform 64-bit
+// base (SGPRs) plus a 32-bit per-lane byte offset.  Issued as inline assembly
+// so that the compiler adds no waits for it; callers order it with explicit
+// s_waitcnt vmcnt.  Nothing else in these kernels uses M0.
 __device__ __forceinline__ void g2lds16s(const void* sbase, uint32_t voff, uint32_t m0v) {
   // readfirstlane returns a signed int: widen through uint32_t so the low
   // half of the address is zero-extended, never sign-extended
@@ -848,8 +838,9 @@ __global__ __launch_bounds__(256) void k_permute_kv(Geom g, const void* k, const
 //    Loads run half a tile (2048 matrix cycles at D = 128) ahead.
 // One thread per row on vector FMAs in one-wave blocks, with K/V tiles staged
 // through LDS by scalar loads, took 9.97 ms for dense attention of 8 heads of
-// 2,442 rows at d = 64 (1.2 TFLOP/s); this kernel 0.204 ms (60 TFLOP/s; the
-// rest is the second round of blocks, 312 over 256 CUs, and exposed loads).
+// 2,442 rows at d = 64 (1.2 TFLOP/s); this kernel 0.204 ms (60 TFLOP/s: its
+// 312 blocks all run at once, 56 of the 256 CUs holding two, so that at most 61%
+// of the chip works, and loads are exposed).
 template <int D, int MODE>
 __global__ __launch_bounds__(256, 2) void k_attn_f32(Geom g, AttnArgs A) {
   constexpr int KT = 32, NQ = D / 8, HQ = NQ / 2, NDB = D / 32;
@@ -1088,16 +1079,16 @@ static AttnArgs make_args(const Work* w, const void* q, const void* k, const voi
 }
 
 template <int D>
-static void attend_d(const Geom& g, const Work* wq, const void* q, const void* k, const void* v,
+static void attend_d(const Geom& g, const Work& w, const void* q, const void* k, const void* v,
                      void* out, hipStream_t s, hipEvent_t* ev) {
-  // every kernel takes all G * BH query heads in one launch (view of query
-  // head 0, whose [G][BH] arrays continue with the other query heads)
+  // every kernel takes all G * BH query heads in one launch (the attend
+  // outputs are [G][BH] arrays)
   const int BQ = g.BH * g.G;
-  const AttnArgs a = make_args(&wq[0], q, k, v, out);
+  const AttnArgs a = make_args(&w, q, k, v, out);
   if (g.bf16) {
     constexpr int CH = D / 8;
     k_permute_kv<D><<<dim3((g.N + 256 / CH - 1) / (256 / CH), g.BH), 256, 0, s>>>(
-        g, k, v, wq[0].permk, wq[0].kperm, wq[0].vperm);
+        g, k, v, w.permk, w.kperm, w.vperm);
   }
   if (ev) (void)hipEventRecord(ev[0], s);
   if (g.bf16) {
@@ -1132,18 +1123,18 @@ static void attend_d(const Geom& g, const Work* wq, const void* q, const void* k
       k_attn_mfma<D, MODE_PROBE><<<gp, 128, 0, s>>>(g, a);
     else
       k_attn_f32<D, MODE_PROBE><<<gp, 256, 0, s>>>(g, a);
-    k_probe_merge<<<dim3(g.M, BQ), 128, 0, s>>>(g, wq[0].part, wq[0].nprobes, wq[0].odp);
+    k_probe_merge<<<dim3(g.M, BQ), 128, 0, s>>>(g, w.part, w.nprobes, w.odp);
   }
   if (ev) (void)hipEventRecord(ev[2], s);
-  launch_fit_correct(g, wq[0], out, s, ev);
+  launch_fit_correct(g, w, out, s, ev);
 }
 
-void launch_attend(const Geom& g, const Work* wq, const void* q, const void* k, const void* v,
+void launch_attend(const Geom& g, const Work& w, const void* q, const void* k, const void* v,
                    void* out, hipStream_t s, hipEvent_t* ev) {
   if (g.d == 64)
-    attend_d<64>(g, wq, q, k, v, out, s, ev);
+    attend_d<64>(g, w, q, k, v, out, s, ev);
   else
-    attend_d<128>(g, wq, q, k, v, out, s, ev);
+    attend_d<128>(g, w, q, k, v, out, s, ev);
 }
 
 template <int D>

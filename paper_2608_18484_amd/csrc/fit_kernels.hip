@@ -575,33 +575,35 @@ __global__ __launch_bounds__(128) void k_probe_scatter(Geom g, Work w, void* out
 }
 
 template <int D>
-static void fit_d(const Geom& g, const Work& w0, void* out, hipStream_t s, hipEvent_t* ev) {
-  // all G * BH query heads in one launch (view of query head 0, whose [G][BH]
-  // arrays continue with the other query heads)
+static void fit_d(const Geom& g, const Work& w, void* out, hipStream_t s, hipEvent_t* ev) {
+  // all G * BH query heads in one launch
   const int BQ = g.BH * g.G;
-  k_fit_prep<D><<<BQ, 1024, 0, s>>>(g, w0);
+  k_fit_prep<D><<<BQ, 1024, 0, s>>>(g, w);
   if (g.M > 0) {  // without probes the statistics are all of the fit
-    k_fit_gram<D><<<dim3((D / 32) * (D / 32), 3, BQ), 256, 0, s>>>(g, w0);
-    // float inputs (whose outputs are held to float rounding) get the double
-    // solve; bf16 inputs the float one
-    if (D <= 64 || !g.bf16)
-      k_fit_solve<D, double><<<dim3(BQ, 2), 1024, 0, s>>>(g, w0);
+    k_fit_gram<D><<<dim3((D / 32) * (D / 32), 3, BQ), 256, 0, s>>>(g, w);
+    // float inputs (whose outputs are held to float rounding) and d = 64 get
+    // the double solve; bf16 inputs of d = 128 the float one
+    auto solve = [&](auto t) { k_fit_solve<D, decltype(t)><<<dim3(BQ, 2), 1024, 0, s>>>(g, w); };
+    if constexpr (D <= 64)
+      solve(0.0);
+    else if (g.bf16)
+      solve(0.f);
     else
-      k_fit_solve<D, float><<<dim3(BQ, 2), 1024, 0, s>>>(g, w0);
-    k_fit_map<D><<<dim3((g.r + 15) / 16, BQ), 1024, 0, s>>>(g, w0);
+      solve(0.0);
+    k_fit_map<D><<<dim3((g.r + 15) / 16, BQ), 1024, 0, s>>>(g, w);
   }
   if (ev) (void)hipEventRecord(ev[3], s);
   const int chunks = row_chunks(g.N, BQ);
-  k_correct<D><<<dim3((g.N + 64 * chunks - 1) / (64 * chunks), BQ), 256, 0, s>>>(g, w0, out, chunks);
-  if (g.M > 0) k_probe_scatter<<<dim3(g.M, BQ), 128, 0, s>>>(g, w0, out);
+  k_correct<D><<<dim3((g.N + 64 * chunks - 1) / (64 * chunks), BQ), 256, 0, s>>>(g, w, out, chunks);
+  if (g.M > 0) k_probe_scatter<<<dim3(g.M, BQ), 128, 0, s>>>(g, w, out);
   if (ev) (void)hipEventRecord(ev[4], s);
 }
 
-void launch_fit_correct(const Geom& g, const Work& w0, void* out, hipStream_t s, hipEvent_t* ev) {
+void launch_fit_correct(const Geom& g, const Work& w, void* out, hipStream_t s, hipEvent_t* ev) {
   if (g.d == 64)
-    fit_d<64>(g, w0, out, s, ev);
+    fit_d<64>(g, w, out, s, ev);
   else
-    fit_d<128>(g, w0, out, s, ev);
+    fit_d<128>(g, w, out, s, ev);
 }
 
 }  // namespace sparsepr

@@ -129,8 +129,7 @@ __device__ void eig_order(const T* A, int* order) {
 // the block reloads the matrix and solves it by cyclic Jacobi instead.
 template <int D>
 __global__ __launch_bounds__(1024) void k_eig_basis(const double* gram, int r, float tau, float* F,
-                                                    float* evals, double* scr, double* rat,
-                                                    int64_t* stats) {
+                                                    double* scr, double* rat, int64_t* stats) {
   using T = typename std::conditional<D <= 64, double, float>::type;
   constexpr int LD = D + 1;
   constexpr int LV = jacobi_vt_ld<D>();
@@ -200,7 +199,6 @@ __global__ __launch_bounds__(1024) void k_eig_basis(const double* gram, int r, f
     const double wgt = (meanv > 0.0 && lam[t] > 0.0) ? sqrt(lam[t] / meanv) : 0.0;
     Fo[i] = wgt > 0.0 ? (float)((double)VT[order[t] * LV + row] * wgt) : 0.f;
   }
-  if (tid < D) evals[(size_t)bh * D + tid] = (float)lam[tid];
 }
 
 // ---------------------------------------------------------------------------
@@ -1225,7 +1223,11 @@ __global__ __launch_bounds__(256) void k_km_update(KmArgs a, int it) {
 // work on a few thousand rows.  Wave w owns rows [w rpw, (w + 1) rpw); the
 // waves' label counts give each label's total, an exclusive scan the group
 // offsets, and every wave then scatters its rows in order as k_sort_scatter
-// does.
+// does.  At the most rows (8,192 in 128 groups) a sort is 17.9 us in this kernel
+// at one head, 18.4 at 24 and 20.7 at 256, against 15.3, 15.8 and 28 in the
+// three kernels plus their two gaps.  With the update in it, 1,024 rows in 16
+// groups take 15 us at one head, 19 at 24 and 47 at 512, against 31, 39 and 63
+// plus three gaps.
 constexpr int kSmallSortWaves = 16;
 constexpr int kSmallSortRows = 8192;
 
@@ -2055,6 +2057,8 @@ __global__ __launch_bounds__(256) void k_sel_choose(Geom g, Work w, int p) {
 // forced cells, then the radix passes of k_sel_hist and k_sel_choose with the
 // cells' keys and costs in registers, instead of 17 launches whose floor (4.8
 // us and a 1.9 us gap each) is far above their work on a few thousand cells.
+// At the most cells (128 x 128) it takes 29 us at one head and 42 at 24 to 256,
+// against 75, 89 and (256 heads) 167 plus the gaps.
 constexpr int kSelSmallCells = 16 * 1024;
 
 __global__ __launch_bounds__(1024) void k_sel_small(Geom g, Work w) {
@@ -2823,13 +2827,12 @@ static void project(const Geom& g, const Work& w, const void* x, const float* F,
 }
 
 // The semantic partitions cluster the raw rows: coordinates phi = I^T x.
-__global__ __launch_bounds__(256) void k_identity_basis(float* F, double* gram, float* evals, int D) {
+__global__ __launch_bounds__(256) void k_identity_basis(float* F, double* gram, int D) {
   const int bh = blockIdx.x;
   for (int i = threadIdx.x; i < D * D; i += 256) {
     F[(size_t)bh * D * D + i] = (i / D == i % D) ? 1.f : 0.f;
     gram[(size_t)bh * D * D + i] = 0.0;
   }
-  for (int i = threadIdx.x; i < D; i += 256) evals[(size_t)bh * D + i] = 0.f;
 }
 
 template <int D>
@@ -2840,11 +2843,10 @@ static void plan_d(const Geom& g, const Work& w, const void* q, const void* k, h
   // Key-response coordinates and the paired K/V partition (Sec. 4.1, App. B.1);
   // the semantic partition clusters the raw keys instead (Sec. 3.1)
   if (g.partition == SPARSEPR_PARTITION_SEMANTIC) {
-    k_identity_basis<<<BH, 256, 0, s>>>(w.fk, w.gram_k, w.evals_k, D);
+    k_identity_basis<<<BH, 256, 0, s>>>(w.fk, w.gram_k, D);
   } else {
     k_key_metric<D><<<dim3(D / 16, BH), 256, 0, s>>>(q, g, w.gram_k);
-    k_eig_basis<D><<<BH, 1024, 0, s>>>(w.gram_k, g.rk, 1e-6f, w.fk, w.evals_k, w.eigscr, w.fitgram,
-                                       w.stats);
+    k_eig_basis<D><<<BH, 1024, 0, s>>>(w.gram_k, g.rk, 1e-6f, w.fk, w.eigscr, w.fitgram, w.stats);
   }
   project<D>(g, w, k, w.fk, g.rk, 0, 0, 0.f, w.phik, s);
   KmArgs ak{w.phik, w.centk, w.labk, w.permk, w.offk, w.blkhist, w.kmstate, g.NV, g.ntext, g.N,
@@ -2856,12 +2858,11 @@ static void plan_d(const Geom& g, const Work& w, const void* q, const void* k, h
                                                          w.kbar, 0);
   if (g.partition == SPARSEPR_PARTITION_RESPONSE) {
     k_query_metric<D><<<dim3(D * D / 2048, BH), 256, 0, s>>>(w.kbar, w.offk, g, w.gram_q);
-    k_eig_basis<D><<<BH, 1024, 0, s>>>(w.gram_q, g.rq, 1e-6f, w.fq, w.evals_q, w.eigscr, w.fitgram,
-                                       w.stats);
+    k_eig_basis<D><<<BH, 1024, 0, s>>>(w.gram_q, g.rq, 1e-6f, w.fq, w.eigscr, w.fitgram, w.stats);
     project<D>(g, w, q, w.fq, g.rq, 1, 1, g.eps_q, w.phiq, s);
   } else {
     // semantic query groups: k-means on the raw queries
-    k_identity_basis<<<BH, 256, 0, s>>>(w.fq, w.gram_q, w.evals_q, D);
+    k_identity_basis<<<BH, 256, 0, s>>>(w.fq, w.gram_q, D);
     project<D>(g, w, q, w.fq, g.rq, 1, 0, 0.f, w.phiq, s);
   }
   KmArgs aq{w.phiq, w.centq, w.labq, w.permq, w.offq, w.blkhist, w.kmstate, g.NV, g.ntext, g.N,

@@ -19,8 +19,6 @@ constexpr int kQTile = 64;
 // Classes of sparse-attention work items, by the 32-row sets of an item: 3,
 // and 2 or 1 (the only class of fp32 items), one launch each.
 constexpr int kItemClasses = 2;
-// Key tile of the attention kernels.
-constexpr int kKTile = 64;
 // Probe-row dense attention: most keys per split (fewer when that leaves the
 // chip idle).
 constexpr int kProbeSplit = 2048;
@@ -59,7 +57,7 @@ struct Geom {
   int nchunk_max;         // attention work items per head (upper bound)
   int psplit, nsplit;     // probe attention: keys per split, key splits
   int part_km;            // the splits' partials live in the k-means operands
-  int nseg;               // key segments of the sparse attention (one launch each)
+  int nseg;               // key segments of the sparse attention (each a launch, or two with classes)
   int nsort_blk;          // counting-sort blocks over NV rows
   int nsort_blk_full;     // counting-sort blocks over N rows
   int cmax;               // max(CKt, CQt)
@@ -71,8 +69,6 @@ struct Geom {
 struct Work {
   double* gram_k;   // [BH][d][d]
   double* gram_q;   // [BH][d][d]
-  float* evals_k;   // [BH][d]
-  float* evals_q;   // [BH][d]
   float* fk;        // [BH][d][rk]
   float* fq;        // [BH][d][rq]
   float* phik;      // [BH][NV][rk]
@@ -166,14 +162,13 @@ void launch_rebuild(const Geom& g, const Work& w, int bh, hipStream_t s);
 // ---- attend kernels -----------------------------------------------------
 // Optional events recorded between the phases of attend (null = none):
 // ev[0] before the sparse attention, ev[1] after it, ev[2] after the probe
-// rows, ev[3] after the fit, ev[4] after the correction.  wq[j] (j < G) is the
-// workspace view holding the attend outputs of query head j of every K/V
-// head; each phase runs for all G query heads in one launch.
-void launch_attend(const Geom& g, const Work* wq, const void* q, const void* k, const void* v,
+// rows, ev[3] after the fit, ev[4] after the correction.
+// Every phase takes the G query heads of each K/V head in the same launches.
+void launch_attend(const Geom& g, const Work& w, const void* q, const void* k, const void* v,
                    void* out, hipStream_t s, hipEvent_t* ev = nullptr);
 // Fit, correction and restore after the sparse and probe attention
 // (records ev[3] after the solve and ev[4] at the end when ev is set).
-void launch_fit_correct(const Geom& g, const Work& w0, void* out, hipStream_t s, hipEvent_t* ev);
+void launch_fit_correct(const Geom& g, const Work& w, void* out, hipStream_t s, hipEvent_t* ev);
 void launch_dense(const Geom& g, const void* q, const void* k, const void* v, void* out,
                   float* part, hipStream_t s);
 

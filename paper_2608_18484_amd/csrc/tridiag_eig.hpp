@@ -38,10 +38,12 @@
 //    correction is small against the gap to the neighbouring eigenvalues
 //    (their quotient bounds the vector's share of them).
 //
-// The float bases of D = 128 keep the sequential forms (tri_reduce, SEQ
-// vectors, tri_back): thousands of k-means decisions per head turn on their
+// The float response bases of D = 128 keep the sequential forms (tri_reduce,
+// SEQ vectors, tri_back): thousands of k-means decisions per head turn on their
 // last bits, and a basis with other roundings, however exact, regroups a few
-// rows of the largest calls.
+// rows of the largest calls.  The response bases of D = 64 and every
+// probe-residual basis (float for bf16 inputs of D = 128, else double) use the
+// others.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <float.h>

@@ -357,8 +357,8 @@ class SparsePR:
 
 
 def dense_attention(q, k, v, out=None, stream=None):
-    """Dense attention (Sec. 3) for every query head on the probe kernels
-    (K and V may have fewer heads: grouped-query attention)."""
+    """Dense attention (Sec. 3) for every query head (K and V may have fewer
+    heads: grouped-query attention)."""
     import torch
     if out is None:
         out = torch.empty_like(q)
