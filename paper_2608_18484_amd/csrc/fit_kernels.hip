@@ -342,7 +342,9 @@ __global__ __launch_bounds__(1024) void k_fit_solve(Geom g, Work w) {
       const double s1 = l1 > 0.0 ? sqrt(l1) : 0.0;
       int rk = 0;
       bool amb = false;
-      for (int t = 0; t < r && t < D; ++t) {
+      // a zero matrix (one probe, or residuals that are all the same) has rank
+      // 0; the search only finds the padding of its empty interval
+      for (int t = 0; t < r && t < D && tw.fnorm > 0.f; ++t) {
         const double lt = tw.lamf[t];
         if (sizeof(T) == 8 && !(lt >= 1e-5 * l1)) amb = true;
         const double st = lt > 0.0 ? sqrt(lt) : 0.0;

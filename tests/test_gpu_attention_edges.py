@@ -234,6 +234,22 @@ def test_fit_map_is_rounded_once(d, rank):
     assert np.mean(ex["fit_bpsi"] == y.astype(np.float32)) > 0.99
 
 
+# one probe leaves no residual about the mean: the basis has rank 0, without the
+# Jacobi solver, and the correction is the probe's residual
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128)])
+@pytest.mark.parametrize("rank", [1, 16])
+def test_fit_of_one_probe(orc, dtype, d, rank):
+    from paper_2608_18484_amd import sparsepr as S
+    wl = medium(grid=(3, 16, 24), heads=1, dtype=dtype, d=d, n_probes=1, resid_rank=rank)
+    r = _run(wl)
+    ex = r["op"].export(0)
+    assert not r["op"].stats()["status_flags"] & S.FLAG_EIG_JACOBI
+    assert ex["fit_rank"] == 0
+    assert np.all(ex["fit_psi"] == 0.0) and np.all(ex["fit_bpsi"] == 0.0)
+    ref, _ = _replay(orc, r, ex, 0, 0)
+    assert rel_l2(r["out"][0, 0], ref) < (1e-5 if dtype == "f32" else 2e-2)
+
+
 # a ridge matrix that is not positive definite: a channel of V that is zero
 # leaves its row and column of the unregularised matrix exactly zero, whatever
 # the other pivots are (noise with fewer probes than dimensions, positive with
